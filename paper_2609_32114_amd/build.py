@@ -33,7 +33,8 @@ FLAGS = [
 # Per-file additions.  The staged walk keeps its MFMA accumulators in
 # architectural registers: its state is rescaled and converted by vector ALU
 # work every step, and accumulation registers would add a copy each way.
-FILE_FLAGS = {"k2_walk.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+FILE_FLAGS = {"k2_walk.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "k2_compact.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def sources():

@@ -229,6 +229,23 @@ bool overlap_applies(bool bf16, bool kda, int Dk, int Dv, bool maps, int N, int 
   return mode == 2 || blocks > 3L * cus;
 }
 
+// Whether a call takes the compact path (csrc/compact.h): GDN in bf16 whose
+// chains are cut into segments, or whose walks (N x Hv x Dv/16 column tiles)
+// outnumber the CUs.  Such calls are bound by memory: the compact factors are
+// 13 KiB per (chunk, value head) block against the affine ones' 96 KiB (d = 128),
+// for three dependent products per chunk instead of one.  us per call, affine
+// against compact: 8 sequences, 34,800 tokens, 32 heads 1124 / 511; 20
+// sequences, 6,100 tokens, 32 heads, raw projections 268 / 115; 1 x 32768
+// tokens, 16 heads (segments) 686 / 339.  With fewer walks each has a CU (or
+// several waves) of its own and the chain's latency decides: those calls keep
+// the affine factors.
+bool compact_applies(bool bf16, bool kda, bool maps, int N, int Hv, int Dv, int cus) {
+  if (!bf16 || kda) return false;
+  if (maps) return true;
+  const long walks = ((long)N * Hv + hagdn::kXcdCount - 1) / hagdn::kXcdCount * hagdn::kXcdCount * (Dv / 16);
+  return walks > cus;
+}
+
 size_t workspace_size(bool kda, int N, int T, int Hqk, int Hv, int Dk, int Dv, int dtype) {
   if (check_shapes(N, T, Hqk, Hv, Dk, Dv, dtype) != HAGDN_OK) return 0;
   Layout L;
@@ -312,6 +329,7 @@ int prefill(bool kda, const void *q, const void *k, const void *v, const float *
   a.ovl_walk_wgs = 0;
   const bool maps = chunks_of(T) > L.seg_chunks;
   const bool overlap = T > 0 && overlap_applies(bf16, kda, Dk, Dv, maps, N, T, Hv, cus);
+  const bool compact = compact_applies(bf16, kda, maps, N, Hv, Dv, cus);
 
   hipStream_t st = static_cast<hipStream_t>(stream_);
   hipEvent_t *ev = nullptr;
@@ -342,6 +360,18 @@ int prefill(bool kda, const void *q, const void *k, const void *v, const float *
     if ((e = mark(6)) != hipSuccess) goto hip_fail;
     if ((e = hagdn::launch_overlapped(a, st)) != hipSuccess) goto hip_fail;
     if ((e = mark(7)) != hipSuccess) goto hip_fail;
+    return HAGDN_OK;
+  }
+  if (compact) {
+    if ((e = hagdn::launch_chunk_compact(a, st)) != hipSuccess) goto hip_fail;
+    if ((e = mark(2)) != hipSuccess) goto hip_fail;
+    if (maps) {
+      if ((e = hagdn::launch_compact_maps(a, st)) != hipSuccess) goto hip_fail;
+      if ((e = mark(3)) != hipSuccess) goto hip_fail;
+    }
+    if ((e = maps ? hagdn::launch_compact_segments(a, st) : hagdn::launch_compact_walk(a, st)) != hipSuccess)
+      goto hip_fail;
+    if ((e = mark(4)) != hipSuccess) goto hip_fail;
     return HAGDN_OK;
   }
   if ((e = hagdn::launch_chunk_local(a, bf16, kda, st)) != hipSuccess) goto hip_fail;
@@ -631,6 +661,10 @@ int hagdn_workspace_region(int kda, int N, int T_total, int Hqk, int Hv, int Dk,
   Layout L;
   if (!make_layout(N, T_total, Hv, Dk, Dv, dtype == HAGDN_BF16 ? 2 : 4, kda != 0, query_cus(), &L))
     return HAGDN_EINVAL;
+  const bool bf16 = dtype == HAGDN_BF16;
+  const bool maps = chunks_of(T_total) > L.seg_chunks;
+  // a compact call keeps none of the affine factors
+  const bool compact = compact_applies(bf16, kda != 0, maps, N, Hv, Dv, query_cus());
   size_t at, next;
   switch (region) {
     case HAGDN_WS_NM: at = L.NM; next = L.Bc; break;
@@ -643,7 +677,7 @@ int hagdn_workspace_region(int kda, int N, int T_total, int Hqk, int Hv, int Dk,
     default: return fail(HAGDN_EINVAL, "unknown workspace region %d", region);
   }
   *offset = at;
-  *bytes = next - at;  // the region plus its alignment padding
+  *bytes = compact && region <= HAGDN_WS_DECAY ? 0 : next - at;  // the region plus its alignment padding
   return HAGDN_OK;
 }
 

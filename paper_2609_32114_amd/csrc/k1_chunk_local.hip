@@ -41,6 +41,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "chunk_item.h"
 #include "device.h"
 #include "prefill.h"
 #include "state_walk.h"
@@ -49,15 +50,6 @@ namespace hagdn {
 
 constexpr int kLocalThreads = 256;
 
-// XOR-swizzled row-major tiles (rows of LD elements, a multiple of 128 bytes):
-// 16-byte chunk q of row r is stored at chunk q ^ (r & 7), so the eight rows
-// a fragment read touches in one LDS cycle hit eight different bank groups
-// with no padding.
-template <typename E, int LD>
-__device__ __forceinline__ int swz(int r, int e) {
-  constexpr int CH = 16 / (int)sizeof(E);
-  return r * LD + ((e / CH) ^ (r & 7)) * CH + e % CH;
-}
 // MFMA fragment: the 8 elements at logical columns e .. e+7 (e a multiple of 8) of row r.
 template <int LD>
 __device__ __forceinline__ bf16x8 frag_sw(const bf16_t *t, int r, int e) {
@@ -124,34 +116,6 @@ __device__ __forceinline__ void gam8(const float *g, int r, int d, float (&x)[8]
     x[e] = lo[e];
     x[4 + e] = hi[e];
   }
-}
-
-// One (chunk, value head) work item: chunk c = item / Hv, head h = item % Hv.
-struct LocalItem {
-  int c, h, start, len;  // len 0: past the last chunk
-};
-// Workgroup b -> item: the value heads of one q/k group (grouped heads share
-// q and k) take consecutive ids of one XCD (ids b, b+8, ... share an XCD and
-// its L2), so all but the first read q and k from L2.  Without grouping this
-// is the identity.  The grid is padded to whole rounds of 8 groups.
-__device__ __forceinline__ LocalItem local_item(const PrefillArgs &a, int b) {
-  LocalItem it{0, 0, 0, 0};
-  const int G = a.Hv / a.Hqk;  // value heads per q/k head
-  const int xcd = b % 8, slot = b / 8;
-  const int grp = (slot / G) * 8 + xcd;  // (chunk, q/k head) group
-  if (grp < a.max_chunks * a.Hqk) {
-    it.c = grp / a.Hqk;
-    it.h = (grp % a.Hqk) * G + slot % G;
-    if (a.single) {  // chunk c of the only sequence (tokens [0, T))
-      it.start = it.c * kChunk;
-      it.len = max(0, min(kChunk, a.T - it.start));
-    } else {
-      const int4 ci = a.chunk_info[it.c];
-      it.start = ci.y;
-      it.len = ci.z;
-    }
-  }
-  return it;
 }
 
 // Overlapped launch: the next item of this XCD's queue.  XCD x serves the
@@ -917,9 +881,7 @@ static hipError_t launch_local_t(const PrefillArgs &a, hipStream_t stream) {
   using L = LocalLayout<T, DK, DV, KDA>;
   hipError_t e = set_lds_limit<T, DK, DV, KDA, PRE>();
   if (e != hipSuccess) return e;
-  // one workgroup per (chunk, value head) block, padded to whole rounds of 8 q/k groups
-  const long groups = (long)a.max_chunks * a.Hqk;
-  const long items = (groups + 7) / 8 * 8 * (a.Hv / a.Hqk);
+  const long items = local_grid(a);
   hipLaunchKernelGGL((chunk_local_kernel<T, DK, DV, KDA, PRE>), dim3((unsigned)items), dim3(kLocalThreads), L::bytes,
                      stream, a);
   return hipGetLastError();

@@ -1,0 +1,231 @@
+// k1_compact.hip -- the first Map phase for the compact path (compact.h): the
+// parts of operators #1-#3 (paper Sec. 2.1: Gate, KKT, Solve) that the state
+// walk cannot redo per column tile, T' = T Diag(b), P' and the decay vectors,
+// for GDN in bf16.  One workgroup of four waves per (chunk, value head).
+//
+// The affine chunk-local kernel (k1_chunk_local.hip) is bound by its factor
+// stores on long calls (96 KiB written per 48 KiB read) and by its dependent
+// phases on short ones.  This one reads keys and queries only, writes 13 KiB,
+// and drops operator #4 and the reduce-side products; what is left is a chain
+// of load, two 64 x 64 products, and the triangular solve.
+//
+// Wave i computes row block i of A and P transposed (token r = 16i + col per
+// lane column), so the P accumulators are P' operand fragments as they stand.
+// It inverts its own diagonal block of I + A from its registers (lane
+// broadcasts, no LDS), then solves COLUMN block i of T: T_ij = -T_ii sum_k A_ik
+// T_kj needs only the wave's own T_kj, so the rows follow one another without
+// a barrier; the last product is taken a second time with its operands
+// swapped, which gives T_ij transposed, the lane order of a T' operand block.
+// Three barriers in all (keys staged, A and the T_ii published, and with raw
+// keys their L2 factors).
+#include "chunk_item.h"
+#include "compact.h"
+
+namespace hagdn {
+namespace {
+
+constexpr int kThreads = 256;
+
+// fp32 16 x 16 x 16 product from operands in accumulator order: a[st] holds
+// A[col][4grp + st], b[st] holds B[4grp + st][col].
+__device__ __forceinline__ f32x4 mma16(f32x4 acc, f32x4 a, f32x4 b) {
+#pragma unroll
+  for (int st = 0; st < 4; ++st) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[st], b[st], acc, 0, 0, 0);
+  return acc;
+}
+
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+
+template <int DK, bool PRE>
+__global__ __launch_bounds__(kThreads, 4) void chunk_compact_kernel(PrefillArgs a) {
+  constexpr int KB = DK / 32, ROW = DK * 2, PIECES = ROW / 16;
+  constexpr int RPB = 1024 / ROW;       // rows of one 1 KiB load
+  constexpr int LPW = kChunk / RPB / 4; // loads per wave
+  __shared__ __align__(16) unsigned char sK[kChunk * ROW];
+  __shared__ __align__(16) float sA[kChunk * kChunk];  // strictly lower blocks: A; diagonal blocks: T_ii
+  __shared__ double sGam[kChunk];
+  __shared__ __align__(16) float sBeta[kChunk], sNk[kChunk];
+  const LocalItem cur = local_item(a, blockIdx.x);
+  if (cur.len <= 0) return;  // past the last chunk: uniform for the workgroup
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = cur.h, start = cur.start, len = cur.len, last = len - 1;
+  const int hk = h / (a.Hv / a.Hqk);
+  const size_t qk_row = (size_t)a.Hqk * DK;
+  const bf16_t *kbase = static_cast<const bf16_t *>(a.k) + (size_t)start * qk_row + (size_t)hk * DK;
+  const bf16_t *qbase = static_cast<const bf16_t *>(a.q) + (size_t)start * qk_row + (size_t)hk * DK;
+
+  // ---- loads: keys to LDS (rows past the chunk's end repeat its last row:
+  //      their b is 0), this lane's query row and token as operands
+#pragma unroll
+  for (int u = 0; u < LPW; ++u) {
+    const int b = wave * LPW + u, r = b * RPB + lane / PIECES;
+    const int piece = (lane % PIECES) ^ row_swz<ROW>(r);
+    lds_copy16(kbase + (size_t)min(r, last) * qk_row + piece * 8, sK + b * 1024);
+  }
+  const int r = 16 * wave + col;  // the token of this lane's column of A^T and P^T
+  bf16x8 qf[KB];
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) qf[kb] = load_frag(qbase + (size_t)min(r, last) * qk_row + kb * 32, grp);
+  if (wave == 0) {
+    const size_t at = (size_t)(start + min(lane, last)) * a.Hv + h;
+    const float graw = a.g[at], braw = a.beta[at];
+    const float gx = (PRE && (a.pre & kPreGateSoftplus)) ? neg_softplus(graw) : graw;
+    const float bx = (PRE && (a.pre & kPreBetaSigmoid)) ? sigmoid(braw) : braw;
+    sBeta[lane] = lane < len ? bx : 0.f;
+    // op #1 in fp64: gamma reaches thousands where gates are near 0, and the
+    // decays are exponentials of its differences
+    double x = lane < len ? gx : 0.f;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const double y = __shfl_up(x, off);
+      if (lane >= off) x += y;
+    }
+    sGam[lane] = x;
+  }
+  wait_loads<0>();
+  __syncthreads();
+
+  auto key_frag = [&](int row, int kb) {  // keys' channels 32kb + 8grp .. +7 of a token row
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(
+        sK + row * ROW + (((4 * kb + grp) ^ row_swz<ROW>(row)) << 4)));
+  };
+  bf16x8 kr[KB];
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) kr[kb] = key_frag(r, kb);
+  float nk = 1.f, nq = 1.f;  // L2 factors of token r's key and query
+  if constexpr (PRE) {
+    if (a.pre & kPreQkNorm) {
+      float ks = 0.f, qs = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float x = frag_elem(kr[kb], j), y = frag_elem(qf[kb], j);
+          ks += x * x;
+          qs += y * y;
+        }
+      ks += __shfl_xor(ks, 16);
+      ks += __shfl_xor(ks, 32);
+      qs += __shfl_xor(qs, 16);
+      qs += __shfl_xor(qs, 32);
+      nk = inv_l2(ks);
+      nq = inv_l2(qs);
+      if (grp == 0) sNk[r] = nk;
+      __syncthreads();
+    }
+  }
+  const double gr = sGam[r];
+  const float br = sBeta[r] * nk;
+
+  // ---- op #2, transposed: A[r][s] and P[r][s], s = 16j + 4grp + e, j <= wave
+  f32x4 accA[4], accP[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    accA[j] = accP[j] = zero4();
+    if (j <= wave) {  // uniform for the wave
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const bf16x8 ks = key_frag(16 * j + col, kb);
+        accA[j] = mma(accA[j], ks, kr[kb]);
+        accP[j] = mma(accP[j], ks, qf[kb]);
+      }
+      f32x4 ns = {1.f, 1.f, 1.f, 1.f};
+      if constexpr (PRE) {
+        if (a.pre & kPreQkNorm) ns = *reinterpret_cast<const f32x4 *>(sNk + 16 * j + 4 * grp);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int s = 16 * j + 4 * grp + e;
+        float dec = s <= r ? __expf((float)(gr - sGam[s])) : 0.f;
+        if constexpr (PRE) dec *= ns[e];
+        accA[j][e] = (s < r && r < len) ? br * accA[j][e] * dec : 0.f;
+        accP[j][e] = s <= r ? accP[j][e] * dec * (a.scale * nq) : 0.f;
+      }
+      if (j < wave) *reinterpret_cast<f32x4 *>(sA + swz<float, kChunk>(r, 16 * j + 4 * grp)) = accA[j];
+    }
+  }
+
+  // ---- op #3, diagonal block: column `col` of (I + A_ii)^-1 by forward
+  //      substitution; A_ii[x][y] sits in lane x + 16 (y / 4), element y % 4
+  f32x4 ad = accA[0];
+#pragma unroll
+  for (int j = 1; j < 4; ++j)
+    if (j == wave) ad = accA[j];
+  float x[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    float acc = i == col ? 1.f : 0.f;
+#pragma unroll
+    for (int s = 0; s < i; ++s) acc -= lane_value(ad[s & 3], i + 16 * (s >> 2)) * x[s];
+    x[i] = acc;
+  }
+  f32x4 tj;  // T_ii in accumulator order: rows 4grp + e, column col
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    tj[e] = grp < 2 ? (grp == 0 ? x[e] : x[4 + e]) : (grp == 2 ? x[8 + e] : x[12 + e]);
+    sA[swz<float, kChunk>(16 * wave + 4 * grp + e, 16 * wave + col)] = tj[e];
+  }
+
+  // ---- P' operand blocks (row tile wave) and the vectors
+  unsigned char *out = static_cast<unsigned char *>(a.NM) + ((size_t)cur.c * a.Hv + h) * kCompactBytes;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+    if (kb <= (wave >> 1))
+      store_frag_at(reinterpret_cast<bf16_t *>(out + kTriBytes + tri_block(wave, kb) * 1024) + lane * 8,
+                    frag_from_acc<bf16_t>(accP[2 * kb], accP[2 * kb + 1]));
+  if (grp == 0) {
+    float *vec = reinterpret_cast<float *>(out + 2 * kTriBytes);
+    const double gl = sGam[kChunk - 1];
+    const float eg = __expf((float)gr);
+    vec[r] = nk * eg;
+    vec[kChunk + r] = nk * __expf((float)(gl - gr));
+    vec[2 * kChunk + r] = a.scale * nq * eg;
+    vec[3 * kChunk + r] = __expf((float)gl);
+  }
+  __syncthreads();
+
+  // ---- op #3, column block j = wave of T, and its T' halves: slots 4 (j & 1)
+  //      .. +3 of the blocks (i, j / 2), lane (col, grp) = T[16i + col][16j + 4grp + e] b_s
+  const f32x4 bs = *reinterpret_cast<const f32x4 *>(sBeta + 16 * wave + 4 * grp);
+  auto put = [&](int i, f32x4 t) {
+    store4(reinterpret_cast<bf16_t *>(out + tri_block(i, wave >> 1) * 1024) + lane * 8 + 4 * (wave & 1), t * bs);
+  };
+  auto rows = [&](int i, int k) {  // block (i, k) of sA: row col, columns 4grp .. +3
+    return *reinterpret_cast<const f32x4 *>(sA + swz<float, kChunk>(16 * i + col, 16 * k + 4 * grp));
+  };
+  put(wave, rows(wave, wave));
+  if (wave & 1) put(wave - 1, zero4());  // the block above the diagonal
+  f32x4 t[4];                            // T_kj, k = wave .. 3
+  t[0] = tj;
+#pragma unroll
+  for (int d = 1; d < 4; ++d) {
+    const int i = wave + d;
+    if (i < 4) {  // uniform for the wave
+      f32x4 y = zero4();
+#pragma unroll
+      for (int k = 0; k < d; ++k) y = mma16(y, rows(i, wave + k), t[k]);
+      const f32x4 tii = rows(i, i);
+      if (i < 3) t[d] = -mma16(zero4(), tii, y);
+      put(i, -mma16(zero4(), y, tii));
+    }
+  }
+}
+
+template <int DK, bool PRE>
+hipError_t launch_t(const PrefillArgs &a, hipStream_t stream) {
+  hipLaunchKernelGGL((chunk_compact_kernel<DK, PRE>), dim3((unsigned)local_grid(a)), dim3(kThreads), 0, stream, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_chunk_compact(const PrefillArgs &a, hipStream_t s) {
+  if (a.max_chunks == 0) return hipSuccess;
+  if (a.Dk == 64) return a.pre ? launch_t<64, true>(a, s) : launch_t<64, false>(a, s);
+  return a.pre ? launch_t<128, true>(a, s) : launch_t<128, false>(a, s);
+}
+
+}  // namespace hagdn

@@ -200,6 +200,12 @@ hipError_t launch_overlapped(const PrefillArgs &a, hipStream_t stream);
 hipError_t launch_state_walk(const PrefillArgs &a, bool kda, int cus, hipStream_t stream);
 // the bf16 segment maps on the staged walk (k2_walk.hip)
 hipError_t launch_seg_maps(const PrefillArgs &a, bool kda, hipStream_t stream);
+// the compact path (compact.h, GDN in bf16): its chunk-local kernel, its
+// whole-chain walk, and its segment maps and per-segment walks
+hipError_t launch_chunk_compact(const PrefillArgs &a, hipStream_t stream);
+hipError_t launch_compact_walk(const PrefillArgs &a, hipStream_t stream);
+hipError_t launch_compact_maps(const PrefillArgs &a, hipStream_t stream);
+hipError_t launch_compact_segments(const PrefillArgs &a, hipStream_t stream);
 // segment-parallel path: segment maps, then ops #5 + #6 per segment
 hipError_t launch_seg_transfer(const PrefillArgs &a, bool bf16, bool kda, hipStream_t stream);
 hipError_t launch_seg_state(const PrefillArgs &a, bool bf16, bool kda, hipStream_t stream);

@@ -1,0 +1,84 @@
+"""GPU: the compact path (GDN in bf16: calls with more walks than compute units,
+and segmented calls) against the general path.
+
+A batch of short sequences with enough value heads takes the compact path; the
+same sequences one by one (few walks, one segment) take the affine factors.
+Both round the operands of every product to bf16 and accumulate in fp32, and
+each is held to 2e-2 of the fp64 oracle elsewhere, so they agree to the sum.
+Lengths sit on the edges of 16-token tiles and 64-token chunks."""
+
+import numpy as np
+import pytest
+
+from gpu_harness import check_against_oracle, run_gpu, to_device
+from paper_2609_32114_amd.inputs import Inputs, make_case
+
+pytestmark = pytest.mark.gpu
+
+LENS = (1, 15, 16, 17, 63, 64, 65, 0, 128, 129, 193)
+
+
+def _alone(inp, n):
+    a, b = int(inp.cu_seqlens[n]), int(inp.cu_seqlens[n + 1])
+    cut = lambda x: np.ascontiguousarray(x[a:b])  # noqa: E731
+    return Inputs(kind=inp.kind, dtype=inp.dtype, q=cut(inp.q), k=cut(inp.k), v=cut(inp.v), g=cut(inp.g),
+                  beta=cut(inp.beta), s0=None if inp.s0 is None else inp.s0[n:n + 1],
+                  cu_seqlens=np.array([0, b - a], dtype=np.int32), scale=inp.scale, meta=dict(inp.meta))
+
+
+def _close(got, ref, what):
+    d = np.max(np.abs(got - ref)) / max(np.max(np.abs(ref)), 1e-30)
+    assert np.all(np.isfinite(got)) and d <= 4e-2, f"{what}: {d:.3e}"
+
+
+@pytest.mark.parametrize("raw", [False, True], ids=["plain", "raw"])
+@pytest.mark.parametrize("dims", [(128, 128), (64, 64), (64, 128), (128, 64)], ids=lambda d: f"{d[0]}x{d[1]}")
+def test_batch_matches_single_sequences(dims, raw):
+    import paper_2609_32114_amd as P
+    Dk, Dv = dims
+    Hqk, Hv = (2, 6) if Dv == 128 else (4, 12)  # 66 or 132 chains: more walks than 256 CUs
+    inp = make_case("gdn", LENS, Hqk, Hv, Dk, Dv, "bf16", with_s0=not raw, seed=51, scale=Dk ** -0.5, raw=raw)
+    pre = P.PRE_ALL if raw else 0
+    assert len(LENS) * Hv * Dv // 16 > 256
+    o, s = run_gpu(inp, preprocess=pre)
+    for n, length in enumerate(LENS):
+        if length == 0:
+            np.testing.assert_array_equal(s[n], inp.s0[n] if inp.s0 is not None else np.zeros_like(s[n]))
+            continue
+        o1, s1 = run_gpu(_alone(inp, n), preprocess=pre)
+        a = int(inp.cu_seqlens[n])
+        _close(o[a:a + length], o1, f"o of sequence {n}")
+        _close(s[n], s1[0], f"state of sequence {n}")
+
+
+@pytest.mark.parametrize("variant", ["lm", "ks", "fg"])
+def test_segments_of_every_count(variant):
+    """2 to 6 segments per sequence (with and without a scan of the maps), the
+    last one ragged, against the oracle."""
+    import paper_2609_32114_amd as P
+    try:
+        P.set_segment_chunks(2)
+        inp = make_case("gdn", (129, 257, 300, 385, 700), 2, 4, 128, 128, "bf16", with_s0=True, variant=variant, seed=52)
+        check_against_oracle(inp, label=f"compact-segments-{variant}")
+    finally:
+        P.set_segment_chunks(0)
+
+
+def test_workspace_regions_of_a_compact_call():
+    import paper_2609_32114_amd as P
+    for T, Hv, held in ((200, 2, True), (32768, 16, False), (4096, 64, False)):
+        for r in (P.WS_NM, P.WS_B, P.WS_QP, P.WS_OLOC, P.WS_DECAY):
+            assert (P.workspace_region("gdn", 1, T, Hv, Hv, 128, 128, P.HAGDN_BF16, r)[1] > 0) == held
+
+
+def test_in_place_state_batch():
+    import torch
+    import paper_2609_32114_amd as P
+    inp = make_case("gdn", (70, 64, 1, 200, 33, 129, 0, 31), 4, 8, 128, 128, "bf16", with_s0=True, variant="s0", seed=53)
+    d = to_device(inp)
+    o1, s1 = P.gdn_prefill(d["q"], d["k"], d["v"], d["g"], d["beta"], initial_state=d["s0"], cu_seqlens=d["cu"])
+    state = d["s0"].clone()
+    o2, _ = P.gdn_prefill(d["q"], d["k"], d["v"], d["g"], d["beta"], initial_state=state, cu_seqlens=d["cu"],
+                          final_out=state)
+    torch.cuda.synchronize()
+    assert torch.equal(o1, o2) and torch.equal(state, s1)
