@@ -231,19 +231,19 @@ bool overlap_applies(bool bf16, bool kda, int Dk, int Dv, bool maps, int N, int 
 
 // Whether a call takes the compact path (csrc/compact.h): GDN in bf16 whose
 // chains are cut into segments, or whose walks (N x Hv x Dv/16 column tiles)
-// outnumber the CUs.  Such calls are bound by memory: the compact factors are
-// 13 KiB per (chunk, value head) block against the affine ones' 96 KiB (d = 128),
-// for three dependent products per chunk instead of one.  us per call, affine
-// against compact: 8 sequences, 34,800 tokens, 32 heads 1124 / 511; 20
-// sequences, 6,100 tokens, 32 heads, raw projections 268 / 115; 1 x 32768
-// tokens, 16 heads (segments) 686 / 339.  With fewer walks each has a CU (or
-// several waves) of its own and the chain's latency decides: those calls keep
-// the affine factors.
+// outnumber half the CUs.  The compact factors are 13 KiB per (chunk, value
+// head) block against the affine ones' 96 KiB (d = 128), for three dependent
+// products per chunk instead of one.  us per call, affine against compact, 256
+// CUs: 1 x 4096 tokens with 20 heads 119 / 86, 32 heads 152 / 95, 64 heads 284 /
+// 150; 4 x 500 tokens, 16 heads 46 / 31; 8 sequences, 34,800 tokens, 32 heads
+// 1124 / 511; 20 sequences, 6,100 tokens, 32 heads, raw projections 268 / 115;
+// 1 x 32768 tokens, 16 heads (segments) 686 / 326.  Up to half the CUs the
+// affine walk's shorter step decides, and its overlapped launch.
 bool compact_applies(bool bf16, bool kda, bool maps, int N, int Hv, int Dv, int cus) {
   if (!bf16 || kda) return false;
   if (maps) return true;
   const long walks = ((long)N * Hv + hagdn::kXcdCount - 1) / hagdn::kXcdCount * hagdn::kXcdCount * (Dv / 16);
-  return walks > cus;
+  return walks > cus / 2;
 }
 
 size_t workspace_size(bool kda, int N, int T, int Hqk, int Hv, int Dk, int Dv, int dtype) {

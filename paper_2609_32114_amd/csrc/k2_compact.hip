@@ -27,7 +27,8 @@ __device__ __forceinline__ void stage_barrier() {
 // query rows.  A ring three chunks deep keeps up to two chunks in flight behind
 // the one in use; at d_k = d_v = 128 with all eight tiles of a head, A three
 // and B two deep take the CU's 160 KiB exactly.
-template <int DK, int CT, bool OUT>
+// RESERVED: LDS bytes the kernel keeps for other use.
+template <int DK, int CT, bool OUT, int RESERVED = 0>
 struct Stage {
   static constexpr int VC = 16 * (CT < 2 ? 2 : CT);  // staged value columns: whole tile pairs
   static constexpr int KROW = DK * 2, VROW = VC * 2;
@@ -42,9 +43,9 @@ struct Stage {
   static constexpr int off_q = off_p + (OUT ? kTriBytes : 0);
   static constexpr int B_BYTES = off_q + (OUT ? kChunk * KROW : 0);
   static constexpr int NA = 3;
-  static constexpr int NB = NA * A_BYTES + 3 * B_BYTES <= kLdsBytes ? 3 : 2;
+  static constexpr int NB = NA * A_BYTES + 3 * B_BYTES + RESERVED <= kLdsBytes ? 3 : 2;
   static constexpr int BYTES = NA * A_BYTES + NB * B_BYTES;
-  static_assert(BYTES <= kLdsBytes, "the rings fit the LDS");
+  static_assert(BYTES + RESERVED <= kLdsBytes, "the rings fit the LDS");
   static constexpr int A_LOADS = A_BYTES / 1024, B_LOADS = B_BYTES / 1024;
   static_assert(A_LOADS < 64, "one chunk's loads fit the vector memory counter");
 };
@@ -115,10 +116,28 @@ struct Span {
 
 // Keeps a ring of D slots filled with the span's chunks: chunk c has landed
 // before the barrier that opens step c, and is loaded behind the barrier that
-// ends the reads of the slot's last tenant.
-template <int D, int LOADS, typename Issue>
+// ends the reads of the slot's last tenant.  ROWS: the row walk's protocol of
+// three barriers a step: chunk c + 1 has landed before the second barrier of
+// step c, and the slot of chunk c is free behind the third.
+template <int D, int LOADS, bool ROWS, typename Issue>
 __device__ __forceinline__ void fill_ring(int nch, Issue issue) {
   static_assert((D - 2) * LOADS < 64, "loads left in flight fit the vector memory counter");
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int c = 0; c < D; ++c)
+      if (c < nch) issue(c);
+    for (int c = -1; c < nch; ++c) {  // step c; -1: before the first one
+      if (c >= 0) stage_barrier();
+      if (c + D - 1 < nch) wait_loads<(D - 2) * LOADS>();  // chunks c + 2 .. c + D - 1 may be in flight
+      else wait_loads<0>();
+      stage_barrier();
+      if (c >= 0) {
+        stage_barrier();
+        if (c + D < nch) issue(c + D);
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int c = 0; c < D - 1; ++c)
     if (c < nch) issue(c);
@@ -132,10 +151,10 @@ __device__ __forceinline__ void fill_ring(int nch, Issue issue) {
 
 // The two loader waves of a workgroup, one per ring; values: columns col0 .. of
 // the head.
-template <int DK, int DV, int CT, bool OUT>
+template <int DK, int DV, int CT, bool OUT, bool ROWS = false, int RESERVED = 0>
 __device__ __forceinline__ void load_chunks(const PrefillArgs &a, const Span &sp, int h, int col0, unsigned char *lds,
                                             int ring, int lane) {
-  using S = Stage<DK, CT, OUT>;
+  using S = Stage<DK, CT, OUT, RESERVED>;
   if (sp.nch <= 0) return;
   const int hk = h / (a.Hv / a.Hqk);
   const size_t kst = (size_t)a.Hqk * DK * 2, vst = (size_t)a.Hv * DV * 2;
@@ -148,14 +167,14 @@ __device__ __forceinline__ void load_chunks(const PrefillArgs &a, const Span &sp
   auto last = [&](int c) { return min(kChunk, sp.len - c * kChunk) - 1; };
   auto fac = [&](int c) { return f0 + (size_t)c * a.Hv * kCompactBytes; };
   if (ring == 0) {
-    fill_ring<S::NA, S::A_LOADS>(sp.nch, [&](int c) {
+    fill_ring<S::NA, S::A_LOADS, ROWS>(sp.nch, [&](int c) {
       unsigned char *st = lds + (c % S::NA) * S::A_BYTES;
       load_rows<S::KROW>(k0 + (size_t)c * kChunk * kst, (uint32_t)kst, last(c), st + S::off_k, lane);
       load_block<kTriBlocks>(fac(c), st + S::off_t, lane);
       load_rows<S::VROW>(v0 + (size_t)c * kChunk * vst, (uint32_t)vst, last(c), st + S::off_v, lane);
     });
   } else {
-    fill_ring<S::NB, S::B_LOADS>(sp.nch, [&](int c) {
+    fill_ring<S::NB, S::B_LOADS, ROWS>(sp.nch, [&](int c) {
       unsigned char *st = lds + S::NA * S::A_BYTES + (c % S::NB) * S::B_BYTES;
       load_block<1>(fac(c) + 2 * kTriBytes, st + S::off_vec, lane);
       if constexpr (OUT) {
@@ -247,12 +266,14 @@ struct TileWalk {
     read_k(st, 0, f[0]);
   }
 
-  // S_c -> S_{c+1}; with OUT also the chunk's outputs, O^T[t][nt]: token
-  // 16nt + col, columns dv_of(tile0 + t, 4grp .. +3).
-  __device__ __forceinline__ void step(const unsigned char *lds, int c, f32x4 (&o)[TW][4]) {
+  // S_c -> S_{c+1}; with OUT also the chunk's outputs, handed to store(o):
+  // O^T[t][nt], token 16nt + col, columns dv_of(tile0 + t, 4grp .. +3).
+  template <typename Store>
+  __device__ __forceinline__ void step(const unsigned char *lds, int c, Store store) {
     const unsigned char *stv = st + S::off_v + voff + vhalf;
     const float *vec = reinterpret_cast<const float *>(sb + S::off_vec);
     int cur = 0;
+    f32x4 o[TW][4];
     // ---- K S_c; meanwhile the state's decay and the value rows
     f32x4 x[TW][4];
     s16x4 v[TW][4];
@@ -348,46 +369,25 @@ struct TileWalk {
 #pragma unroll
       for (int kb = KB / 2; kb < KB; ++kb) {
         if (kb + 1 < KB) read_q(sb, kb + 1, f[cur ^ 1]);
-        else read_kt(st, 0, 0, f[cur ^ 1]);
         mul_q(kb);
         cur ^= 1;
       }
       mix<KB / 2 * 4 * TW, 3>();
+      cur ^= 1;  // (the last group read nothing ahead)
     }
-    // ---- S_{c+1} = e^gamma_last S_c + K^T Diag(kd) U; meanwhile the output's scale
-    constexpr int NQ = RT / 4;  // row tile quarters
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const bool lastg = kb == 1 && q == NQ - 1;
-        if (!lastg) read_kt(st, q + 1 < NQ ? kb : kb + 1, q + 1 < NQ ? q + 1 : 0, f[cur ^ 1]);
-        else if constexpr (OUT) read_tri(sb + S::off_p, f[cur ^ 1]);
-        if constexpr (OUT) {
-          if (kb == 0) {
-#pragma unroll
-            for (int nt = 4 / NQ * q; nt < 4 / NQ * (q + 1); ++nt) {
-              const float eq = vec[2 * kChunk + 16 * nt + col];
-#pragma unroll
-              for (int t = 0; t < TW; ++t) o[t][nt] = o[t][nt] * eq;
-            }
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int t = 0; t < TW; ++t) H[t][4 * q + i] = mma(H[t][4 * q + i], f[cur][i], ud[t][kb]);
-        mix<4 * TW, 3>();
-        cur ^= 1;
-      }
-    // ---- O = Diag(eq) Q S_c + P' U; meanwhile S_{c+1} as operands, behind the
-    //      barrier the next chunk's first keys
-    stage_barrier();  // chunk c + 1 has landed; every read of chunk c is done
-    slots(lds, c + 1);
-    read_k(st, 0, f[cur ^ 1]);
+    // ---- O = Diag(eq) Q S_c + P' U, stored during the state update: behind the
+    //      step's barrier the loaders' burst of loads fills the address unit, and
+    //      a store there held its wave for a fifth of the step
     if constexpr (OUT) {
+      read_tri(sb + S::off_p, f[cur ^ 1]);
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) round_state(kb);
+      for (int nt = 0; nt < 4; ++nt) {
+        const float eq = vec[2 * kChunk + 16 * nt + col];
+#pragma unroll
+        for (int t = 0; t < TW; ++t) o[t][nt] = o[t][nt] * eq;
+      }
+      cur ^= 1;
+      read_kt(st, 0, 0, f[cur ^ 1]);
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -395,8 +395,44 @@ struct TileWalk {
 #pragma unroll
           for (int t = 0; t < TW; ++t) o[t][nt] = mma(o[t][nt], uf[t][kb], f[cur][tri_block(nt, kb)]);
       mix<6 * TW, 3>();
+      cur ^= 1;
     }
-    if (cur == 0) {  // the next step starts from buffer 0
+    // ---- S_{c+1} = e^gamma_last S_c + K^T Diag(kd) U; behind the barrier the next
+    //      chunk's first keys
+    constexpr int NQ = RT / 4;  // row tile quarters
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const bool lastg = kb == 1 && q == NQ - 1;
+        if (!lastg) {
+          read_kt(st, q + 1 < NQ ? kb : kb + 1, q + 1 < NQ ? q + 1 : 0, f[cur ^ 1]);
+          if constexpr (OUT) {
+            if (kb == 0 && q == 0) store(o);
+          }
+        } else {
+          stage_barrier();  // chunk c + 1 has landed; every read of chunk c is done
+          slots(lds, c + 1);
+          read_k(st, 0, f[cur ^ 1]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int t = 0; t < TW; ++t) H[t][4 * q + i] = mma(H[t][4 * q + i], f[cur][i], ud[t][kb]);
+        if constexpr (OUT) {
+          if (kb == 1 && q > 0) {
+            round_state(2 * q - 2);
+            round_state(2 * q - 1);
+          }
+        }
+        mix<4 * TW, 3>();
+        cur ^= 1;
+      }
+    if constexpr (OUT) {
+      round_state(KB - 2);
+      round_state(KB - 1);
+    }
+    if (cur == 1) {  // the next step starts from buffer 0
 #pragma unroll
       for (int i = 0; i < 4; ++i) f[0][i] = f[1][i];
     }
@@ -491,9 +527,7 @@ __global__ __launch_bounds__(64 * (NW + 2), 1) void compact_walk_kernel(PrefillA
     const int orow = (col * a.Hv + h) * DV * 2 + dv_of(tile0, 4 * grp) * 2, ostep = 16 * (int)row_bytes;
     w.begin(lds);
     for (int c = 0; c < sp.nch; ++c) {
-      f32x4 o[TW][4];
-      w.step(lds, c, o);
-      store_chunk<TW>(orsrc, orow + 4 * c * ostep, ostep, o);
+      w.step(lds, c, [&](const f32x4(&o)[TW][4]) { store_chunk<TW>(orsrc, orow + 4 * c * ostep, ostep, o); });
     }
   }
   if (a.s_final && sg.w == ss.y - 1) {
@@ -504,6 +538,238 @@ __global__ __launch_bounds__(64 * (NW + 2), 1) void compact_walk_kernel(PrefillA
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           a.s_final[sbase + (size_t)dk_of(rt, 4 * grp + e) * DV + dv_of(tile0 + t, col)] = w.H[t][rt][e];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Row walk: the latency form of the state walk, for calls whose column tiles do
+// not outnumber the CUs much.  Four waves share TW tiles: wave w owns token tile
+// w of K S, X, U and O and state row tiles w RT/4 .. of the update, so the three
+// dependent products of a step are a few MFMAs each, and S, X and U pass
+// between the waves as operand fragments through LDS (three barriers a step).
+// A step takes ~2,000 cycles (62 us for 64 chunks), against ~3,200 for one wave
+// per tile: the LDS moves ~160 KiB in it at about 128 bytes a clock (operands in
+// and out, exchange).  Q, T' and P' straight to their one reader's registers (two
+// chunks ahead, or one behind a loader that touched their lines) took 74 and
+// 78 us: the waits for those loads cost more than the LDS bytes they save.
+template <int DK, int TW>
+struct RowExchange {
+  static constexpr int KB = DK / 32;
+  static constexpr int off_s = 0, off_x = TW * KB * 1024, off_u = off_x + TW * 2048, off_d = off_u + TW * 2048;
+  static constexpr int BYTES = off_d + TW * 2048;
+};
+
+template <int DK, int DV, int TW, bool SINGLE>
+__global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
+  constexpr int NG = DV / (16 * TW), RT = DK / 16, KB = DK / 32, RPW = RT / 4;
+  using X = RowExchange<DK, TW>;
+  using S = Stage<DK, TW, true, X::BYTES>;
+  extern __shared__ __align__(16) unsigned char lds[];
+  single_status<SINGLE>(a);
+  const int b = blockIdx.x;
+  const int pair = (b / kXcds / NG) * kXcds + b % kXcds;  // the workgroups of a head share an XCD
+  const int tg = (b / kXcds) % NG;
+  if (pair >= a.N * a.Hv) return;  // uniform for the workgroup
+  const int n = pair / a.Hv, h = pair % a.Hv;
+  const int4 si = seq_info_at<SINGLE>(a, n);  // {first chunk, chunks, start, length}
+  const Span sp{si.x, si.y, si.z, si.w};
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int tile0 = tg * TW;
+  if (w >= 4) {
+    load_chunks<DK, DV, TW, true, true, X::BYTES>(a, sp, h, 32 * (tile0 >> 1), lds, w - 4, lane);
+    return;
+  }
+  const int col = lane & 15, grp = lane >> 4;
+  f32x4 H[TW][RPW];  // rows dk_of(w RPW + i, 4grp + e)
+  const size_t sbase = ((size_t)n * a.Hv + h) * DK * DV;
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        H[t][i][e] = a.s0 ? a.s0[sbase + (size_t)dk_of(w * RPW + i, 4 * grp + e) * DV + dv_of(tile0 + t, col)] : 0.f;
+
+  // LDS addresses, from a slot's base: key / query rows of token tile w, the
+  // transposed keys of this wave's row tiles, the transposed values
+  int koff[KB], ktoff[RPW];
+  const int tr = 4 * grp + (col >> 2);
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb)
+    koff[kb] = (16 * w + col) * S::KROW + (((4 * kb + grp) ^ row_swz<S::KROW>(col)) << 4);
+#pragma unroll
+  for (int i = 0; i < RPW; ++i) {
+    const int rt = w * RPW + i;
+    ktoff[i] = tr * S::KROW + (((4 * (rt >> 1) + (col & 3)) ^ row_swz<S::KROW>(tr)) << 4) + 8 * (rt & 1);
+  }
+  const int voff = (16 * w + tr) * S::VROW + (((col & 3) ^ row_swz<S::VROW>(16 * w + tr)) << 4) + (TW == 1 ? 8 * (tile0 & 1) : 0);
+  const bool low = w >= 2;  // token tiles 2, 3 also meet the triangles' second k-block
+  const int tri0 = tri_block(w, 0) * 1024 + lane * 16, tri1 = low ? tri0 + 1024 : tri0;
+  unsigned char *xch = lds + S::BYTES;
+  unsigned char *xs = xch + X::off_s + lane * 16, *xx = xch + X::off_x + lane * 16, *xu = xch + X::off_u + lane * 16,
+                *xd = xch + X::off_d + lane * 16;
+  const int half = (w >> 1) * 1024 + 8 * (w & 1);  // this token tile's half of a fragment
+  auto put_half = [](unsigned char *p, f32x4 v) {
+    *reinterpret_cast<u32x2 *>(p) = __builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4));
+  };
+  const bf16x8 zero = zero_frag<bf16_t>();
+
+  const size_t row_bytes = (size_t)a.Hv * DV * 2;
+  const __amdgpu_buffer_rsrc_t orsrc =
+      rows_buffer(static_cast<unsigned char *>(a.o) + (size_t)sp.tok0 * row_bytes, (uint32_t)(sp.len * row_bytes));
+  int ooff = ((16 * w + col) * a.Hv + h) * DV * 2 + dv_of(tile0, 4 * grp) * 2;
+  // ---- operands of chunk c, each read behind the barrier after its last use
+  bf16x8 kf[KB], qf[KB], tf[2], pf[2], kt[RPW][2];
+  s16x4 v[TW];
+  f32x4 ek;
+  auto slot_a = [&](int c) { return lds + __builtin_amdgcn_readfirstlane((c % S::NA) * S::A_BYTES); };
+  auto slot_b = [&](int c) {
+    return lds + __builtin_amdgcn_readfirstlane(S::NA * S::A_BYTES + (c % S::NB) * S::B_BYTES);
+  };
+  auto read_keys = [&](int c) {
+    const unsigned char *st = slot_a(c);
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) kf[kb] = lds_frag(st + S::off_k + koff[kb]);
+#pragma unroll
+    for (int t = 0; t < TW; ++t) v[t] = read_tr(st + S::off_v + voff + 8 * t);
+    ek = *reinterpret_cast<const f32x4 *>(slot_b(c) + S::off_vec + (16 * w + 4 * grp) * 4);
+  };
+  auto read_queries = [&](int c) {
+    const unsigned char *sb = slot_b(c);
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) qf[kb] = lds_frag(sb + S::off_q + koff[kb]);
+  };
+  auto put_state = [&]() {
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      if constexpr (RPW == 2) {
+        *reinterpret_cast<u32x4 *>(xs + (t * KB + w) * 1024) =
+            __builtin_bit_cast(u32x4, frag_from_acc<bf16_t>(H[t][0], H[t][1]));
+      } else {
+        put_half(xs + t * KB * 1024 + half, H[t][0]);
+      }
+    }
+  };
+  if (sp.nch > 0) {
+    stage_barrier();  // chunk 0 has landed
+    read_keys(0);
+    read_queries(0);
+    put_state();
+  }
+  for (int c = 0; c < sp.nch; ++c) {
+    const unsigned char *st = slot_a(c), *sb = slot_b(c);
+    const float *vec = reinterpret_cast<const float *>(sb + S::off_vec);
+    stage_barrier();  // S_c is there
+    bf16x8 hb[TW][KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int t = 0; t < TW; ++t) hb[t][kb] = lds_frag(xs + (t * KB + kb) * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+    tf[0] = lds_frag(st + S::off_t + tri0);
+    tf[1] = lds_frag(st + S::off_t + tri1);
+    const f32x4 kd = *reinterpret_cast<const f32x4 *>(vec + kChunk + 16 * w + 4 * grp);
+    const float dec = vec[3 * kChunk], eq = vec[2 * kChunk + 16 * w + col];
+    // ---- X = V - Diag(ek) K S_c (two chains over the k-blocks)
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      f32x4 x0 = zero4(), x1 = zero4();
+#pragma unroll
+      for (int kb = 0; kb < KB; kb += 2) {
+        x0 = mma(x0, kf[kb], hb[t][kb]);
+        x1 = mma(x1, kf[kb + 1], hb[t][kb + 1]);
+      }
+      put_half(xx + t * 2048 + half, to_f32(v[t]) - ek * (x0 + x1));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- Q S_c and the decay, while X crosses
+    f32x4 o[TW];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      f32x4 q0 = zero4(), q1 = zero4();
+#pragma unroll
+      for (int kb = 0; kb < KB; kb += 2) {
+        q0 = mma(q0, hb[t][kb], qf[kb]);
+        q1 = mma(q1, hb[t][kb + 1], qf[kb + 1]);
+      }
+      o[t] = q0 + q1;
+    }
+    stage_barrier();  // X is there, and chunk c + 1 has landed
+    // ---- U = T' X
+    bf16x8 xf[TW][2];
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) xf[t][kb] = lds_frag(xx + (2 * t + kb) * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        const unsigned char *p = st + S::off_k + ktoff[i] + 32 * kb * S::KROW;
+        kt[i][kb] = frag_of(read_tr(p), read_tr(p + 16 * S::KROW));
+      }
+    pf[0] = lds_frag(sb + S::off_p + tri0);
+    pf[1] = lds_frag(sb + S::off_p + tri1);
+    if (!low) tf[1] = pf[1] = zero;
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      f32x4 u = mma(zero4(), tf[0], xf[t][0]);
+      u = mma(u, tf[1], xf[t][1]);
+      put_half(xd + t * 2048 + half, u * kd);
+      put_half(xu + t * 2048 + half, u);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      o[t] = o[t] * eq;
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) H[t][i] = H[t][i] * dec;
+    }
+    stage_barrier();  // U is there
+    // ---- S_{c+1} = e^gamma_last S_c + K^T Diag(kd) U, then O = Diag(eq) Q S_c + P' U
+    bf16x8 df[TW][2], uf[TW][2];
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) df[t][kb] = lds_frag(xd + (2 * t + kb) * 1024);
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) uf[t][kb] = lds_frag(xu + (2 * t + kb) * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+    read_keys(c + 1);
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) H[t][i] = mma(H[t][i], kt[i][kb], df[t][kb]);
+    put_state();
+    __builtin_amdgcn_sched_barrier(0);
+    read_queries(c + 1);
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      o[t] = mma(o[t], uf[t][0], pf[0]);
+      o[t] = mma(o[t], uf[t][1], pf[1]);
+    }
+    if constexpr (TW == 2) {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, frag_from_acc<bf16_t>(o[0], o[1])), orsrc, ooff, 0,
+                                             0);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, __builtin_convertvector(o[0], bf16x4)), orsrc, ooff,
+                                            0, 0);
+    }
+    ooff += kChunk * (int)row_bytes;
+  }
+  if (a.s_final) {
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          a.s_final[sbase + (size_t)dk_of(w * RPW + i, 4 * grp + e) * DV + dv_of(tile0 + t, col)] = H[t][i][e];
   }
 }
 
@@ -551,8 +817,7 @@ __device__ __forceinline__ void map_tiles(const PrefillArgs &a, int s, int h, in
   if (nch > 0) {
     w.begin(lds);
     for (int c = 0; c < nch; ++c) {
-      f32x4 o[2][4];
-      w.step(lds, c, o);
+      w.step(lds, c, [](const f32x4(&)[2][4]) {});
     }
   }
   stage_barrier();  // every read of the rings is done
@@ -697,6 +962,20 @@ hipError_t launch_walk_t(const PrefillArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <int DK, int DV, int TW, bool SINGLE>
+hipError_t launch_row_t(const PrefillArgs &a, hipStream_t stream) {
+  using X = RowExchange<DK, TW>;
+  constexpr int lds = Stage<DK, TW, true, X::BYTES>::BYTES + X::BYTES;
+  const void *kern = reinterpret_cast<const void *>(&compact_row_kernel<DK, DV, TW, SINGLE>);
+  static std::atomic<bool> done[kMaxDevices];
+  hipError_t e = raise_lds(kern, lds, done);
+  if (e != hipSuccess) return e;
+  const long groups = ((long)a.N * a.Hv + kXcds - 1) / kXcds;
+  const long blocks = groups * kXcds * (DV / (16 * TW));
+  hipLaunchKernelGGL((compact_row_kernel<DK, DV, TW, SINGLE>), dim3((unsigned)blocks), dim3(64 * 6), lds, stream, a);
+  return hipGetLastError();
+}
+
 template <int DK, int DV, bool SINGLE>
 hipError_t launch_map_t(const PrefillArgs &a, hipStream_t stream) {
   constexpr int rings = Stage<DK, DV / 16, false>::BYTES, tr = DK * (DK + 8) * 2;
@@ -724,6 +1003,14 @@ hipError_t launch_dims(const PrefillArgs &a, Part part, hipStream_t s) {
   constexpr int NW = DV / 32;
   if (part == Part::kMaps) return launch_map_t<DK, DV, SINGLE>(a, s);
   if (part == Part::kSegments) return launch_walk_t<DK, DV, 2, NW, SINGLE, true>(a, s);
+  // The row walk while the column tiles, one or two to a workgroup, fit the CUs
+  // in one round; beyond that a whole head per workgroup, which moves each
+  // operand once for all its tiles.  Walk of 64 chunks, us, row walk against the
+  // whole head: 32 heads 69 / 124 (one tile), 48 heads 90 / 127 and 64 heads 104
+  // / 129 (two tiles).
+  const long tiles = ((long)a.N * a.Hv + kXcds - 1) / kXcds * kXcds * (DV / 16);
+  if (tiles <= a.cus) return launch_row_t<DK, DV, 1, SINGLE>(a, s);
+  if (tiles <= 2L * a.cus) return launch_row_t<DK, DV, 2, SINGLE>(a, s);
   return launch_walk_t<DK, DV, 2, NW, SINGLE, false>(a, s);
 }
 

@@ -1,8 +1,10 @@
-"""GPU: the compact path (GDN in bf16: calls with more walks than compute units,
-and segmented calls) against the general path.
+"""GPU: the compact path (GDN in bf16: calls with more walks than half the compute
+units, and segmented calls) against the general path.
 
-A batch of short sequences with enough value heads takes the compact path; the
-same sequences one by one (few walks, one segment) take the affine factors.
+A batch of short sequences with enough value heads takes the compact path, in
+each of its three walks (four waves on one column tile or two, up to 256 and 512
+tiles; beyond them a whole head per workgroup); the same sequences one by one
+(few walks, one segment) take the affine factors.
 Both round the operands of every product to bf16 and accumulate in fp32, and
 each is held to 2e-2 of the fp64 oracle elsewhere, so they agree to the sum.
 Lengths sit on the edges of 16-token tiles and 64-token chunks."""
@@ -32,14 +34,16 @@ def _close(got, ref, what):
 
 
 @pytest.mark.parametrize("raw", [False, True], ids=["plain", "raw"])
+@pytest.mark.parametrize("heads", [2, 4, 6])
 @pytest.mark.parametrize("dims", [(128, 128), (64, 64), (64, 128), (128, 64)], ids=lambda d: f"{d[0]}x{d[1]}")
-def test_batch_matches_single_sequences(dims, raw):
+def test_batch_matches_single_sequences(dims, heads, raw):
     import paper_2609_32114_amd as P
     Dk, Dv = dims
-    Hqk, Hv = (2, 6) if Dv == 128 else (4, 12)  # 66 or 132 chains: more walks than 256 CUs
+    Hv = heads * (128 // Dv)
+    Hqk = Hv // 2
     inp = make_case("gdn", LENS, Hqk, Hv, Dk, Dv, "bf16", with_s0=not raw, seed=51, scale=Dk ** -0.5, raw=raw)
     pre = P.PRE_ALL if raw else 0
-    assert len(LENS) * Hv * Dv // 16 > 256
+    assert 128 < len(LENS) * Hv * Dv // 16
     o, s = run_gpu(inp, preprocess=pre)
     for n, length in enumerate(LENS):
         if length == 0:
