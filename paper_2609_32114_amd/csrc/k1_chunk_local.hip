@@ -34,10 +34,10 @@
 // <= 1, and upper-triangle products (which may overflow) are discarded by
 // selection.
 //
-// Wave roles (4 waves): wave i computes row block i of A and P; wave 0 then
-// solves T by forward substitution (lane j owns column j) while waves 1-3
-// write the decay; wave i computes token block i of W and U~ into LDS; then
-// the four reduce-side products are split over the waves.
+// Wave roles (4 waves): wave i computes row block i of A and P, inverts its
+// diagonal block of I + A and solves column block i of T; wave i computes token
+// block i of W and U~ into LDS; then the four reduce-side products are split
+// over the waves.
 #include <algorithm>
 #include <atomic>
 
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
   constexpr int V = 16 / (int)sizeof(T);  // elements per 16-byte vector
   constexpr int KT = DK / 16, VT = DV / 16;
   constexpr int KPW = KT / 4;             // d_k tiles per wave in the reduce-side products
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, grp = lane >> 4;
   // overlapped launch: walk workgroups also produce one chunk-local item
   // first, while the first chunks are being computed everywhere
@@ -399,10 +399,9 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
   if constexpr (PRE) {
     if (a.pre & kPreQkNorm) qscale = in.l2norm_q();
   }
-  f32x4 accP[4];
+  f32x4 accP[4], accA[4];
   {
     const int i = wave, r = rq;
-    f32x4 accA[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) accA[j] = accP[j] = zero4();
     if constexpr (!KDA) {
@@ -577,6 +576,15 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
       }
     }
   }
+  // op #3, diagonal blocks: T_ii of this wave's block from its accumulators, over
+  // A's diagonal block (which nobody else reads)
+  f32x4 ad = accA[0];
+#pragma unroll
+  for (int j = 1; j < 4; ++j)
+    if (j == wave) ad = accA[j];  // uniform for the wave
+  const f32x4 tw0 = invert_unit_lower(ad);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) sA[swz<float, L::LDA>(16 * wave + 4 * grp + e, 16 * wave + col)] = tw0[e];
   __syncthreads();
   // KDA: beta of the tokens this lane scales T's columns by in op #4 (no LDS
   // copy: the gate table fills it); loaded here, used after the solve
@@ -592,59 +600,40 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
         bs[kb][j] = s < len ? bx : 0.f;
       }
   }
-  // keys as channel rows over the token rows op #2 is done with (region X)
+  // keys as channel rows over the token rows op #2 is done with (region X);
+  // KDA: K * e^gamma, op #4's operand, formed here once per element.  Formed by
+  // every wave as it read its operands, the exponentials and their table reads
+  // were a quarter of the item's vector instructions.
 #pragma unroll
   for (int it = 0; it < NKV; ++it) {
     const int cv = wave * (DK / 4) + it * V;
     const uint4 u = __builtin_bit_cast(uint4, kv[it]);
 #pragma unroll
-    for (int j = 0; j < V; ++j) sKt[swz<T, L::LDT>(cv + j, lane)] = V16::raw(u, j);
+    for (int j0 = 0; j0 < V; j0 += 4) {
+      f32x4 gq = zero4();
+      if constexpr (KDA) gq = *reinterpret_cast<const f32x4 *>(sGam + gam_at<DK>(lane, cv + j0));
+#pragma unroll
+      for (int j = j0; j < j0 + 4; ++j)
+        sKt[swz<T, L::LDT>(cv + j, lane)] =
+            KDA ? Elt<T>::from_f32(V16::get(u, j) * __expf(gq[j - j0])) : V16::raw(u, j);
+    }
   }
 
-  // ---- op #3: T = (I + A)^-1 (unit lower triangular, fp32), blocked by 16.
-  //      Diagonal blocks: wave w inverts block w by forward substitution (lane
-  //      j < 16 solves column j).  Then block rows i = 1..3: wave j < i forms
-  //      T_ij = -T_ii sum_{k=j}^{i-1} A_ik T_kj with fp32 MFMA (16x16x4), and
-  //      block row i overwrites A's block row i, which later rows never read.
-  if (lane < 16) {
-    const int b0 = 16 * wave, j = lane;
-    float x[16];
+  // ---- op #3: T = (I + A)^-1 over A in place (chunk_item.h); every read of A
+  //      ends before T's off-diagonal blocks overwrite it
+  {
+    f32x4 tt[3];
+    solve_column(sA, wave, tw0, [&](int i, f32x4 t) {
+      const int d = i - wave;  // 1 .. 3
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float acc = (r == j) ? 1.f : 0.f;
+      for (int u = 0; u < 3; ++u)
+        if (u + 1 == d) tt[u] = t;
+    });
+    __syncthreads();
 #pragma unroll
-      for (int s = 0; s < r; ++s) acc -= sA[swz<float, L::LDA>(b0 + r, b0 + s)] * x[s];
-      x[r] = acc;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sA[swz<float, L::LDA>(b0 + r, b0 + j)] = x[r];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 1; i < 4; ++i) {
-    f32x4 res = zero4();
-    if (wave < i) {
-      const int j = wave;
-      f32x4 y = zero4();  // sum_k A_ik T_kj
-      for (int k = j; k < i; ++k) {
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-          const float av = sA[swz<float, L::LDA>(16 * i + col, 16 * k + 4 * st + grp)];
-          const float tv = sA[swz<float, L::LDA>(16 * k + 4 * st + grp, 16 * j + col)];
-          y = __builtin_amdgcn_mfma_f32_16x16x4f32(av, tv, y, 0, 0, 0);
-        }
-      }
-      // T_ii y: the accumulator rows 4grp + st of y are the k index of step st
-#pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        const float tv = sA[swz<float, L::LDA>(16 * i + col, 16 * i + 4 * grp + st)];
-        res = __builtin_amdgcn_mfma_f32_16x16x4f32(tv, y[st], res, 0, 0, 0);
-      }
-    }
-    __syncthreads();  // every read of block row i of A is done
-    if (wave < i) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sA[swz<float, L::LDA>(16 * i + 4 * grp + e, 16 * wave + col)] = -res[e];
+    for (int u = 0; u < 3; ++u) {
+      const int i = wave + 1 + u;
+      if (i < 4) *reinterpret_cast<f32x4 *>(sA + swz<float, L::LDA>(16 * i + col, 16 * wave + 4 * grp)) = tt[u];
     }
     __syncthreads();
   }
@@ -691,19 +680,7 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
       f32x4 acc = zero4();
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
-        Frag<T> kf;
-        if constexpr (!KDA) {
-          kf = frag_sw<L::LDT>(sKt, d, kb * 32 + 8 * grp);
-        } else {
-          float xk[8];
-          const Frag<T> kraw = frag_sw<L::LDT>(sKt, d, kb * 32 + 8 * grp);  // tokens kc(grp, 0..7)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int s = kb * 32 + kc(grp, j);
-            xk[j] = frag_elem(kraw, j) * __expf(sGam[gam_at<DK>(s, d)]);
-          }
-          kf = make_frag<T>(xk);
-        }
+        const Frag<T> kf = frag_sw<L::LDT>(sKt, d, kb * 32 + 8 * grp);
         acc = mma(acc, tw[kb], kf);
       }
       store4(sWt + swz<T, L::LDT>(d, tpos), acc);
@@ -714,9 +691,25 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
   }
   // ---- Kt = (K * e^(gamma_last - gamma))^T in place of the staged keys, tokens
   //      kmap-permuted like sWt / sUt (kmap moves tokens only inside their
-  //      32-token block).  Thread tid < 2 DK takes channel row tid % DK and
-  //      32-token block tid / DK, so at d_k = 128 all four waves share it.
-  if (tid < DK * (kChunk / 32)) {
+  //      32-token block).  GDN: thread tid < 2 DK takes channel row tid % DK and
+  //      32-token block tid / DK, so at d_k = 128 all four waves share it.  KDA:
+  //      from the keys in registers (region X holds K * e^gamma).
+  if constexpr (KDA) {
+    const int pos = (lane & 32) + kmap_pos(lane & 31);
+#pragma unroll
+    for (int it = 0; it < NKV; ++it) {
+      const int cv = wave * (DK / 4) + it * V;
+      const uint4 u = __builtin_bit_cast(uint4, kv[it]);
+#pragma unroll
+      for (int j0 = 0; j0 < V; j0 += 4) {
+        const f32x4 gl = *reinterpret_cast<const f32x4 *>(sGam + gam_at<DK>(kChunk - 1, cv + j0));
+        const f32x4 gq = *reinterpret_cast<const f32x4 *>(sGam + gam_at<DK>(lane, cv + j0));
+#pragma unroll
+        for (int j = j0; j < j0 + 4; ++j)
+          sKt[swz<T, L::LDT>(cv + j, pos)] = Elt<T>::from_f32(V16::get(u, j) * __expf(gl[j - j0] - gq[j - j0]));
+      }
+    }
+  } else if (tid < DK * (kChunk / 32)) {
     constexpr int UH = 32 / V;  // 16-byte vectors per 32-token block
     const int d = tid % DK, base = 32 * (tid / DK);
     uint4 row[UH];
@@ -729,9 +722,7 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
       for (int j = 0; j < V; ++j) {
         const int p = u * V + j;            // position inside the 32-token block
         const int s = kmap(p >> 3, p & 7);  // token held there, relative to base
-        const float ex = KDA ? __expf(sGam[gam_at<DK>(kChunk - 1, d)] - sGam[gam_at<DK>(base + s, d)])
-                             : sKdec[base + s];
-        outv[j] = V16::get(row[s / V], s % V) * ex;
+        outv[j] = V16::get(row[s / V], s % V) * sKdec[base + s];
       }
       *reinterpret_cast<uint4 *>(sKt + swz<T, L::LDT>(d, base + u * V)) = V16::pack(outv);
     }

@@ -11,11 +11,8 @@
 //
 // Wave i computes row block i of A and P transposed (token r = 16i + col per
 // lane column), so the P accumulators are P' operand fragments as they stand.
-// It inverts its own diagonal block of I + A from its registers (lane
-// broadcasts, no LDS), then solves COLUMN block i of T: T_ij = -T_ii sum_k A_ik
-// T_kj needs only the wave's own T_kj, so the rows follow one another without
-// a barrier; the last product is taken a second time with its operands
-// swapped, which gives T_ij transposed, the lane order of a T' operand block.
+// It then inverts its diagonal block and solves column block i of T
+// (chunk_item.h), whose transposed blocks are halves of T' operand blocks.
 // Three barriers in all (keys staged, A and the T_ii published, and with raw
 // keys their L2 factors).
 #include "chunk_item.h"
@@ -25,18 +22,6 @@ namespace hagdn {
 namespace {
 
 constexpr int kThreads = 256;
-
-// fp32 16 x 16 x 16 product from operands in accumulator order: a[st] holds
-// A[col][4grp + st], b[st] holds B[4grp + st][col].
-__device__ __forceinline__ f32x4 mma16(f32x4 acc, f32x4 a, f32x4 b) {
-#pragma unroll
-  for (int st = 0; st < 4; ++st) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[st], b[st], acc, 0, 0, 0);
-  return acc;
-}
-
-__device__ __forceinline__ float lane_value(float x, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
-}
 
 template <int DK, bool PRE>
 __global__ __launch_bounds__(kThreads, 4) void chunk_compact_kernel(PrefillArgs a) {
@@ -154,20 +139,9 @@ __global__ __launch_bounds__(kThreads, 4) void chunk_compact_kernel(PrefillArgs 
 #pragma unroll
   for (int j = 1; j < 4; ++j)
     if (j == wave) ad = accA[j];
-  float x[16];
+  const f32x4 tj = invert_unit_lower(ad);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    float acc = i == col ? 1.f : 0.f;
-#pragma unroll
-    for (int s = 0; s < i; ++s) acc -= lane_value(ad[s & 3], i + 16 * (s >> 2)) * x[s];
-    x[i] = acc;
-  }
-  f32x4 tj;  // T_ii in accumulator order: rows 4grp + e, column col
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    tj[e] = grp < 2 ? (grp == 0 ? x[e] : x[4 + e]) : (grp == 2 ? x[8 + e] : x[12 + e]);
-    sA[swz<float, kChunk>(16 * wave + 4 * grp + e, 16 * wave + col)] = tj[e];
-  }
+  for (int e = 0; e < 4; ++e) sA[swz<float, kChunk>(16 * wave + 4 * grp + e, 16 * wave + col)] = tj[e];
 
   // ---- P' operand blocks (row tile wave) and the vectors
   unsigned char *out = static_cast<unsigned char *>(a.NM) + ((size_t)cur.c * a.Hv + h) * kCompactBytes;
@@ -193,25 +167,9 @@ __global__ __launch_bounds__(kThreads, 4) void chunk_compact_kernel(PrefillArgs 
   auto put = [&](int i, f32x4 t) {
     store4(reinterpret_cast<bf16_t *>(out + tri_block(i, wave >> 1) * 1024) + lane * 8 + 4 * (wave & 1), t * bs);
   };
-  auto rows = [&](int i, int k) {  // block (i, k) of sA: row col, columns 4grp .. +3
-    return *reinterpret_cast<const f32x4 *>(sA + swz<float, kChunk>(16 * i + col, 16 * k + 4 * grp));
-  };
-  put(wave, rows(wave, wave));
+  put(wave, block_rows(sA, wave, wave));
   if (wave & 1) put(wave - 1, zero4());  // the block above the diagonal
-  f32x4 t[4];                            // T_kj, k = wave .. 3
-  t[0] = tj;
-#pragma unroll
-  for (int d = 1; d < 4; ++d) {
-    const int i = wave + d;
-    if (i < 4) {  // uniform for the wave
-      f32x4 y = zero4();
-#pragma unroll
-      for (int k = 0; k < d; ++k) y = mma16(y, rows(i, wave + k), t[k]);
-      const f32x4 tii = rows(i, i);
-      if (i < 3) t[d] = -mma16(zero4(), tii, y);
-      put(i, -mma16(zero4(), y, tii));
-    }
-  }
+  solve_column(sA, wave, tj, [&](int i, f32x4 tt) { put(i, tt); });
 }
 
 template <int DK, bool PRE>
