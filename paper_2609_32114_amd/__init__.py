@@ -140,7 +140,22 @@ def workspace_size(kind, N, T, Hqk, Hv, Dk, Dv, dtype_code) -> int:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _raw_stream(device_index):
+    """The hipStream_t of torch's current stream on the device, as an int."""
+    import torch
+    get = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # no Stream object on the way
+    return get(device_index) if get is not None else torch.cuda.current_stream(device_index).cuda_stream
+
+
+def _on(device_index, *tensors):
+    """Whether every tensor is contiguous and on this GPU."""
+    for t in tensors:
+        if t.get_device() != device_index or not t.is_contiguous():
+            return False
+    return device_index >= 0
 
 
 def _check_buffer(name, t, device, dtype, shape):
@@ -156,17 +171,16 @@ def _check_buffer(name, t, device, dtype, shape):
         raise ValueError(f"{name} must be contiguous")
 
 
-def _prefill(kind, q, k, v, g, beta, initial_state, cu_seqlens, scale, output_final_state,
-             workspace, out, final_out, preprocess=0):
+def _check_prefill(kind, q, k, v, g, beta):
+    """The input checks one by one, for their messages."""
     import torch
-    lib = load_library()
     if not (q.is_cuda and k.is_cuda and v.is_cuda and g.is_cuda and beta.is_cuda):
         raise ValueError("all tensors must be on the GPU")
     if not all(t.device == q.device for t in (k, v, g, beta)):
         raise ValueError("q, k, v, g and beta must be on one device")
     if not (q.dtype == k.dtype == v.dtype):
         raise TypeError("q, k, v must share one dtype")
-    dt = _dtype_code(q.dtype)
+    _dtype_code(q.dtype)
     if g.dtype != torch.float32 or beta.dtype != torch.float32:
         raise TypeError("g and beta must be float32")
     for name, t in (("q", q), ("k", k), ("v", v), ("g", g), ("beta", beta)):
@@ -179,14 +193,34 @@ def _prefill(kind, q, k, v, g, beta, initial_state, cu_seqlens, scale, output_fi
     gshape = (T, Hv) if kind == "gdn" else (T, Hv, Dk)
     if tuple(g.shape) != gshape or tuple(beta.shape) != (T, Hv):
         raise ValueError(f"g must be {gshape} and beta {(T, Hv)}")
+
+
+def _prefill(kind, q, k, v, g, beta, initial_state, cu_seqlens, scale, output_final_state,
+             workspace, out, final_out, preprocess=0):
+    import torch
+    lib = _lib or load_library()
+    f32, di = torch.float32, q.get_device()
+    qs, vs = q.shape, v.shape
+    if not (_on(di, q, k, v, g, beta) and q.dtype is k.dtype is v.dtype and g.dtype is f32 and beta.dtype is f32
+            and len(qs) == 3 and len(vs) == 3 and k.shape == qs and vs[0] == qs[0]
+            and g.shape == ((vs[0], vs[1]) if kind == "gdn" else (vs[0], vs[1], qs[2]))
+            and beta.shape == (vs[0], vs[1])):
+        _check_prefill(kind, q, k, v, g, beta)
+    dt = _dtype_code(q.dtype)
+    T, Hqk, Dk = qs
+    Hv, Dv = vs[1], vs[2]
     dev = q.device
     if cu_seqlens is None:
-        cu_seqlens = torch.tensor([0, T], dtype=torch.int32, device=dev)
-    if cu_seqlens.dtype != torch.int32 or not cu_seqlens.is_cuda or not cu_seqlens.is_contiguous():
-        raise TypeError("cu_seqlens must be a contiguous int32 GPU tensor")
-    if cu_seqlens.device != dev or cu_seqlens.dim() != 1:
-        raise ValueError(f"cu_seqlens must be a 1-D tensor on {dev}")
-    N = cu_seqlens.shape[0] - 1
+        # [0, T] from a kernel: a copy from the host would wait for the stream
+        cu_seqlens = (torch.arange(0, 2 * T, T, dtype=torch.int32, device=dev) if 0 < T < 1 << 30 else
+                      torch.tensor([0, T], dtype=torch.int32, device=dev))
+        N = 1
+    else:
+        if cu_seqlens.dtype != torch.int32 or not cu_seqlens.is_cuda or not cu_seqlens.is_contiguous():
+            raise TypeError("cu_seqlens must be a contiguous int32 GPU tensor")
+        if cu_seqlens.get_device() != di or cu_seqlens.dim() != 1:
+            raise ValueError(f"cu_seqlens must be a 1-D tensor on {dev}")
+        N = cu_seqlens.shape[0] - 1
     state_shape = (N, Hv, Dk, Dv)
     if initial_state is not None:
         _check_buffer("initial_state", initial_state, dev, torch.float32, state_shape)
@@ -199,16 +233,17 @@ def _prefill(kind, q, k, v, g, beta, initial_state, cu_seqlens, scale, output_fi
             _check_buffer("final_out", final_out, dev, torch.float32, state_shape)
         sf = final_out if final_out is not None else torch.empty(state_shape, dtype=torch.float32,
                                                                  device=dev)
-    need = workspace_size(kind, N, T, Hqk, Hv, Dk, Dv, dt)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    elif not workspace.is_cuda or workspace.device != dev or not workspace.is_contiguous():
-        raise ValueError(f"workspace must be a contiguous tensor on {dev}")
-    stream = torch.cuda.current_stream(dev).cuda_stream
+        workspace = torch.empty(workspace_size(kind, N, T, Hqk, Hv, Dk, Dv, dt), dtype=torch.uint8, device=dev)
+    else:
+        if Dk not in (64, 128) or Dv not in (64, 128) or N < 1 or Hqk < 1 or Hv % Hqk or not 0 < Hv < 65536:
+            workspace_size(kind, N, T, Hqk, Hv, Dk, Dv, dt)  # raises (the call itself checks the given size)
+        if not workspace.is_cuda or workspace.get_device() != di or not workspace.is_contiguous():
+            raise ValueError(f"workspace must be a contiguous tensor on {dev}")
     fn = lib.gdn_prefill_ex if kind == "gdn" else lib.kda_prefill_ex
-    rc = fn(_ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta), _ptr(initial_state), _ptr(cu_seqlens),
-            N, T, Hqk, Hv, Dk, Dv, float(scale), dt, int(preprocess), _ptr(o), _ptr(sf),
-            _ptr(workspace), workspace.numel() * workspace.element_size(), ctypes.c_void_p(stream))
+    rc = fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), g.data_ptr(), beta.data_ptr(), _ptr(initial_state),
+            cu_seqlens.data_ptr(), N, T, Hqk, Hv, Dk, Dv, float(scale), dt, int(preprocess), o.data_ptr(), _ptr(sf),
+            workspace.data_ptr(), workspace.numel() * workspace.element_size(), _raw_stream(di))
     if rc != 0:
         raise HagdnError(rc, _err(lib))
     return o, sf
@@ -231,15 +266,15 @@ def kda_prefill(q, k, v, g, beta, initial_state=None, cu_seqlens=None, scale=1.0
                     workspace, out, final_out, preprocess)
 
 
-def _decode(kind, q, k, v, g, beta, state, slots, scale, preprocess, out):
+def _check_decode(kind, q, k, v, g, beta, state):
+    """The input checks one by one, for their messages."""
     import torch
-    lib = load_library()
     for name, t in (("q", q), ("k", k), ("v", v), ("g", g), ("beta", beta), ("state", state)):
         if not t.is_cuda or not t.is_contiguous() or t.device != q.device:
             raise ValueError(f"{name} must be a contiguous tensor on {q.device}")
     if not (q.dtype == k.dtype == v.dtype):
         raise TypeError("q, k, v must share one dtype")
-    dt = _dtype_code(q.dtype)
+    _dtype_code(q.dtype)
     if g.dtype != torch.float32 or beta.dtype != torch.float32 or state.dtype != torch.float32:
         raise TypeError("g, beta and state must be float32")
     N, Hqk, Dk = q.shape
@@ -251,20 +286,34 @@ def _decode(kind, q, k, v, g, beta, state, slots, scale, preprocess, out):
         raise ValueError(f"g must be {gshape} and beta {(N, Hv)}")
     if state.dim() != 4 or tuple(state.shape[1:]) != (Hv, Dk, Dv):
         raise ValueError(f"state must be [slots, {Hv}, {Dk}, {Dv}]")
+
+
+def _decode(kind, q, k, v, g, beta, state, slots, scale, preprocess, out):
+    import torch
+    lib = _lib or load_library()
+    f32, di = torch.float32, q.get_device()
+    qs, vs, ss = q.shape, v.shape, state.shape
+    if not (_on(di, q, k, v, g, beta, state) and q.dtype is k.dtype is v.dtype
+            and g.dtype is f32 and beta.dtype is f32 and state.dtype is f32
+            and len(qs) == 3 and len(vs) == 3 and k.shape == qs and vs[0] == qs[0]
+            and g.shape == ((vs[0], vs[1]) if kind == "gdn" else (vs[0], vs[1], qs[2]))
+            and beta.shape == (vs[0], vs[1]) and len(ss) == 4 and ss[1:] == (vs[1], qs[2], vs[2])):
+        _check_decode(kind, q, k, v, g, beta, state)
+    dt = _dtype_code(q.dtype)
+    N, Hqk, Dk = qs
+    Hv, Dv = vs[1], vs[2]
     if slots is None:
-        if state.shape[0] < N:
+        if ss[0] < N:
             raise ValueError("without slots the state pool needs one state per sequence")
-    elif slots.dtype != torch.int32 or not slots.is_cuda or tuple(slots.shape) != (N,) \
-            or not slots.is_contiguous() or slots.device != q.device:
+    elif slots.dtype != torch.int32 or not slots.is_cuda or slots.shape != (N,) \
+            or not slots.is_contiguous() or slots.get_device() != di:
         raise TypeError(f"slots must be a contiguous int32 tensor of length N on {q.device}")
     if out is not None:
         _check_buffer("out", out, q.device, q.dtype, (N, Hv, Dv))
     o = out if out is not None else torch.empty((N, Hv, Dv), dtype=q.dtype, device=q.device)
-    stream = torch.cuda.current_stream(q.device).cuda_stream
     fn = lib.gdn_decode if kind == "gdn" else lib.kda_decode
-    rc = fn(_ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta), _ptr(state), _ptr(slots),
-            int(state.shape[0]), N, Hqk, Hv, Dk, Dv, float(scale), dt, int(preprocess), _ptr(o),
-            ctypes.c_void_p(stream))
+    rc = fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), g.data_ptr(), beta.data_ptr(), state.data_ptr(), _ptr(slots),
+            ss[0], N, Hqk, Hv, Dk, Dv, float(scale), dt, int(preprocess), o.data_ptr(), _raw_stream(di))
     if rc != 0:
         raise HagdnError(rc, _err(lib))
     return o
