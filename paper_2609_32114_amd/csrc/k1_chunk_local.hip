@@ -176,7 +176,7 @@ struct LocalIn {
   static constexpr int NKV = DK / 4 / V, NVV = DV / 4 / V;       // 16-byte vectors per lane
   static constexpr int GPT = KDA ? kChunk * DK / kLocalThreads : 1;  // gate values per thread
   u32x4 kv[NKV], vv[NVV];  // keys, values: lane = token, wave = channel quarter
-  float bval, gk[GPT];     // beta of token tid (KDA: of token 16 wave + col); gates (KDA: thread = (channel, token segment))
+  float bval, gk[GPT];     // beta of token tid (KDA: of token `lane`, in every wave); gates (KDA: thread = (channel, token segment))
   Frag<T> qf[DK / 32];     // queries of token 16 wave + col, op #2 operand
   f32x4 qacc[DK / 16];     // the same queries in accumulator layout (channels 16m + 4grp ..)
 
@@ -199,9 +199,9 @@ struct LocalIn {
       const u32x4 x = *reinterpret_cast<const u32x4 *>(vb + i * V);
       vv[i] = live ? x : u32x4{0, 0, 0, 0};
     }
-    // GDN: thread tid < 64 holds beta of token tid (staged in LDS); KDA: each
-    // lane holds beta of its op #2 token 16 wave + col
-    const int bt = KDA ? 16 * wave + (lane & 15) : tid;
+    // GDN: thread tid < 64 holds beta of token tid (staged in LDS); KDA: every
+    // wave holds all of them, one per lane
+    const int bt = KDA ? lane : tid;
     const float b = a.beta[(size_t)(it.start + min(bt & (kChunk - 1), last)) * a.Hv + it.h];
     const float bx = (PRE && (a.pre & kPreBetaSigmoid)) ? sigmoid(b) : b;
     bval = (bt < kChunk && bt < it.len) ? bx : 0.f;
@@ -294,8 +294,10 @@ struct LocalIn {
 // its XCD's queue and publishes the block's ready flag once its factors are
 // stored; workgroups below a.ovl_walk_wgs then walk a whole chain
 // (ovl_walk).
+// Workgroups per CU asked of the compiler: KDA in bf16 as many as its LDS allows,
+// two (d_k = 128, 80 KiB) or three.
 template <typename T, int DK, int DV, bool KDA, bool PRE, int OVL = 0>
-__global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 : 1) void chunk_local_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(kLocalThreads, OVL ? 2 : !(KDA && sizeof(T) == 2) ? 1 : DK == 64 ? 3 : 2) void chunk_local_kernel(PrefillArgs a) {
   using L = LocalLayout<T, DK, DV, KDA>;
   using V16 = Vec16<T>;
   using In = LocalIn<T, DK, DV, KDA, PRE>;
@@ -564,12 +566,13 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
           }
         }
       }
+      const float br = __shfl(bval, r);  // beta of token r
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int s = 16 * j + 4 * grp + e;
-          accA[j][e] = (j <= i && s < r) ? bval * accA[j][e] : 0.f;  // bval: beta of token r
+          accA[j][e] = (j <= i && s < r) ? br * accA[j][e] : 0.f;
           accP[j][e] = (j <= i && s <= r) ? accP[j][e] * qscale : 0.f;
         }
         *reinterpret_cast<f32x4 *>(sA + swz<float, L::LDA>(r, 16 * j + 4 * grp)) = accA[j];
@@ -586,20 +589,6 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
 #pragma unroll
   for (int e = 0; e < 4; ++e) sA[swz<float, L::LDA>(16 * wave + 4 * grp + e, 16 * wave + col)] = tw0[e];
   __syncthreads();
-  // KDA: beta of the tokens this lane scales T's columns by in op #4 (no LDS
-  // copy: the gate table fills it); loaded here, used after the solve
-  float bs[KDA ? 2 : 1][8];
-  if constexpr (KDA) {
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int s = kb * 32 + kc(grp, j);
-        const float b = a.beta[(size_t)(start + min(s, len - 1)) * a.Hv + h];
-        const float bx = (PRE && (a.pre & kPreBetaSigmoid)) ? sigmoid(b) : b;
-        bs[kb][j] = s < len ? bx : 0.f;
-      }
-  }
   // keys as channel rows over the token rows op #2 is done with (region X);
   // KDA: K * e^gamma, op #4's operand, formed here once per element.  Formed by
   // every wave as it read its operands, the exponentials and their table reads
@@ -656,7 +645,8 @@ __global__ __launch_bounds__(kLocalThreads, OVL || (KDA && sizeof(T) == 2) ? 2 :
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int s = kb * 32 + kc(grp, j);
-        const float t = trow[j] * (KDA ? bs[kb][j] : sBeta[s]);
+        // KDA has no LDS left for beta: from the lane that holds token s
+        const float t = trow[j] * (KDA ? __shfl(bval, s) : sBeta[s]);
         xu[j] = t;
         xw[j] = KDA ? t : t * __expf((float)sGd[s]);
       }
