@@ -84,9 +84,10 @@ static hipError_t dispatch_dims(const PrefillArgs &a, hipStream_t s) {
 
 hipError_t launch_state_prop(const PrefillArgs &a, bool bf16, bool kda, hipStream_t s) {
   if (bf16) {
-    // more walks than CUs: the staged walk, several tiles per workgroup
+    // more walks than CUs: the staged walk, several tiles per workgroup (KDA;
+    // GDN calls take the compact path from half the CUs on)
     const long walks = ((long)a.N * a.Hv + kXcds - 1) / kXcds * kXcds * (a.Dv / 16);
-    if (walks > a.cus) return launch_state_walk(a, kda, a.cus, s);
+    if (kda && walks > a.cus) return launch_state_walk(a, a.cus, s);
     return kda ? dispatch_dims<bf16_t, true>(a, s) : dispatch_dims<bf16_t, false>(a, s);
   }
   return kda ? dispatch_dims<float, true>(a, s) : dispatch_dims<float, false>(a, s);

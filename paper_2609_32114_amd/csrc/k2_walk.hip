@@ -1,4 +1,5 @@
-// k2_walk.hip -- staged walks (bf16): the Reduce phase of chunkwise
+// k2_walk.hip -- staged walks (KDA in bf16; GDN takes the compact path,
+// k2_compact.hip): the Reduce phase of chunkwise
 // delta-rule prefill (paper Sec. 2.1, operator #5 H) with one wave per
 // 16-column tile and the chunk's shared operands staged in LDS by a loader
 // wave.  Two kernels:
@@ -58,8 +59,8 @@ __device__ __forceinline__ void walk_store4(__amdgpu_buffer_rsrc_t r, int off, f
 // products.  The chunk's NM and Q' blocks, read by every tile of the head,
 // reach LDS through direct memory-to-LDS loads that a loader wave issues two
 // chunks ahead into a three-stage ring; TPW tiles of one head share a
-// workgroup and its stages.  Each tile wave fetches its own B and O_loc (and
-// the GDN decay) into registers two chunks ahead.
+// workgroup and its stages.  Each tile wave fetches its own B and O_loc into
+// registers two chunks ahead.
 //
 // One step c of a tile wave: S_c as bf16 B fragments -> S <- D S + B -> o of
 // chunk c-1 stored -> for each k-block kb: S += NM(:, kb) S_c(kb) and
@@ -68,11 +69,11 @@ __device__ __forceinline__ void walk_store4(__amdgpu_buffer_rsrc_t r, int off, f
 // barrier, B_(c+1): chunk c+1 has landed and every read of stage c is done
 // (the loader then refills it), and chunk c+1's first fragments are read
 // behind it while the last products run.
-template <typename T, int DK, bool KDA, bool QP = true>
+template <typename T, int DK, bool QP = true>
 struct WalkStage {
   static constexpr int NM_BYTES = DK * DK * (int)sizeof(T);
   static constexpr int QP_BYTES = QP ? kChunk * DK * (int)sizeof(T) : 0;
-  static constexpr int DEC_BYTES = KDA ? DK * 4 : 0;
+  static constexpr int DEC_BYTES = DK * 4;
   static constexpr int NM_OPS = NM_BYTES / 1024, QP_OPS = QP_BYTES / 1024;  // 16-byte lane loads
   static constexpr int DEC_OPS = DEC_BYTES / 256;                            // 4-byte lane loads
   static constexpr int OPS = NM_OPS + QP_OPS + DEC_OPS;  // loads per chunk
@@ -106,13 +107,12 @@ template <typename T, int DK>
 struct WalkLaneOps {
   uint2 b[DK / 16];  // B rows 16rt + 4grp .. +3 of this tile (raw bf16)
   uint2 ol[4];       // O_loc, token tile nt, d_v rows 4grp .. +3 of this tile
-  float dec;         // GDN decay of the chunk
 };
 
-template <typename T, int DK, int DV, bool KDA, bool SINGLE, int TPW>
+template <typename T, int DK, int DV, bool SINGLE, int TPW>
 __global__ __launch_bounds__(64 * (TPW + 1), 1) void state_walk_kernel(PrefillArgs a) {
   static_assert(sizeof(T) == 2, "the staged walk is the bf16 path");
-  using S = WalkStage<T, DK, KDA>;
+  using S = WalkStage<T, DK>;
   constexpr int RT = DK / 16, KB = DK / 32, NG = DV / (16 * TPW);
   extern __shared__ __align__(16) unsigned char lds[];
   single_status<SINGLE>(a);
@@ -141,11 +141,9 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void state_walk_kernel(PrefillAr
         for (int j = 0; j < S::NM_OPS; ++j) lds_load16(nm + j * 1024, st + j * 1024);
 #pragma unroll
         for (int j = 0; j < S::QP_OPS; ++j) lds_load16(qp + j * 1024, st + S::NM_BYTES + j * 1024);
-        if constexpr (KDA) {
 #pragma unroll
-          for (int j = 0; j < S::DEC_OPS; ++j)
-            lds_load4(a.dec + bk * DK + j * 64 + lane, st + S::NM_BYTES + S::QP_BYTES + j * 256);
-        }
+        for (int j = 0; j < S::DEC_OPS; ++j)
+          lds_load4(a.dec + bk * DK + j * 64 + lane, st + S::NM_BYTES + S::QP_BYTES + j * 256);
       };
       issue(0);
       issue(1);
@@ -193,7 +191,6 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void state_walk_kernel(PrefillAr
         op.ol[2 * i] = make_uint2(v[0], v[1]);
         op.ol[2 * i + 1] = make_uint2(v[2], v[3]);
       }
-      if constexpr (!KDA) op.dec = a.dec[bk * DK];
     };
     WalkLaneOps<T, DK> ring[2];
     fetch(ring[0], 0);
@@ -234,12 +231,8 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void state_walk_kernel(PrefillAr
       for (int kb = 0; kb < KB; ++kb) hb[kb] = frag_from_acc<T>(H[2 * kb], H[2 * kb + 1]);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        f32x4 d;
-        if constexpr (KDA) {
-          d = *reinterpret_cast<const f32x4 *>(stl - lane * 16 + S::NM_BYTES + S::QP_BYTES + (16 * rt + 4 * grp) * 4);
-        } else {
-          d = f32x4{ring[u].dec, ring[u].dec, ring[u].dec, ring[u].dec};
-        }
+        const f32x4 d =
+            *reinterpret_cast<const f32x4 *>(stl - lane * 16 + S::NM_BYTES + S::QP_BYTES + (16 * rt + 4 * grp) * 4);
         H[rt] = d * H[rt] + raw4_to_f32(ring[u].b[rt]);
       }
       store_out(c - 1);
@@ -295,11 +288,11 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void state_walk_kernel(PrefillAr
 // follows get a map, and the first segment has no A: its B_seg walk starts
 // from the initial state (copied to s0c on the way, prefill.h).  A is stored in NM's fragment order (bf16) through an LDS transpose,
 // B_seg in fp32 in the state kernel's tile order (prefill.h).
-template <typename T, int DK, int DV, bool KDA, bool SINGLE, int TPW>
+template <typename T, int DK, int DV, bool SINGLE, int TPW>
 __global__ __launch_bounds__(64 * (TPW + 1), 1) void seg_map_kernel(PrefillArgs a) {
   static_assert(sizeof(T) == 2, "the staged walk is the bf16 path");
   static_assert(TPW % 2 == 0, "A's fragment blocks pair adjacent column tiles");
-  using S = WalkStage<T, DK, KDA, false>;
+  using S = WalkStage<T, DK, false>;
   constexpr int RT = DK / 16, KB = DK / 32;
   constexpr int NA = DK / (16 * TPW), NB = DV / (16 * TPW);  // workgroups per map
   extern __shared__ __align__(16) unsigned char lds[];
@@ -328,10 +321,8 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void seg_map_kernel(PrefillArgs 
         const unsigned char *nm = NMg + bk * S::NM_BYTES + lane * 16;
 #pragma unroll
         for (int j = 0; j < S::NM_OPS; ++j) lds_load16(nm + j * 1024, st + j * 1024);
-        if constexpr (KDA) {
 #pragma unroll
-          for (int j = 0; j < S::DEC_OPS; ++j) lds_load4(a.dec + bk * DK + j * 64 + lane, st + S::NM_BYTES + j * 256);
-        }
+        for (int j = 0; j < S::DEC_OPS; ++j) lds_load4(a.dec + bk * DK + j * 64 + lane, st + S::NM_BYTES + j * 256);
       };
       issue(0);
       issue(1);
@@ -374,7 +365,6 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void seg_map_kernel(PrefillArgs 
     const T *__restrict__ Bg = static_cast<const T *>(a.Bc);
     struct Lane {
       uint2 b[RT];  // B rows 16rt + 4grp .. +3 of tile t (B_seg walks only)
-      float dec;    // GDN decay of the chunk
     };
     auto fetch = [&](Lane &op, int c) {
       const size_t bk = blk(c);
@@ -390,7 +380,6 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void seg_map_kernel(PrefillArgs 
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) op.b[rt] = make_uint2(0u, 0u);
       }
-      if constexpr (!KDA) op.dec = a.dec[bk * DK];
     };
     Lane ring[2];
     fetch(ring[0], 0);
@@ -411,17 +400,12 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void seg_map_kernel(PrefillArgs 
       Frag<T> hb[KB];
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) hb[kb] = frag_from_acc<T>(H[2 * kb], H[2 * kb + 1]);
-      f32x4 dk[KDA ? RT : 1];
-      if constexpr (KDA) {
+      f32x4 dk[RT];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          dk[rt] = *reinterpret_cast<const f32x4 *>(stl - lane * 16 + S::NM_BYTES + (16 * rt + 4 * grp) * 4);
-      }
+      for (int rt = 0; rt < RT; ++rt)
+        dk[rt] = *reinterpret_cast<const f32x4 *>(stl - lane * 16 + S::NM_BYTES + (16 * rt + 4 * grp) * 4);
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const f32x4 d = KDA ? dk[KDA ? rt : 0] : f32x4{ring[u].dec, ring[u].dec, ring[u].dec, ring[u].dec};
-        H[rt] = d * H[rt] + raw4_to_f32(ring[u].b[rt]);
-      }
+      for (int rt = 0; rt < RT; ++rt) H[rt] = dk[rt] * H[rt] + raw4_to_f32(ring[u].b[rt]);
       fetch(ring[u], c + 2);
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
@@ -490,10 +474,10 @@ __global__ __launch_bounds__(64 * (TPW + 1), 1) void seg_map_kernel(PrefillArgs 
 // would not fit beside them, so the waves issue the stage loads themselves
 // (load j by wave j mod D/16), as the last memory operations of a step, and
 // wait for their share of the next chunk before its barrier.
-template <typename T, int D, bool KDA, bool SINGLE>
+template <typename T, int D, bool SINGLE>
 __global__ __launch_bounds__(64 * (D / 16), 1) void seg_pair_kernel(PrefillArgs a) {
   static_assert(sizeof(T) == 2, "the staged walk is the bf16 path");
-  using S = WalkStage<T, D, KDA, false>;
+  using S = WalkStage<T, D, false>;
   constexpr int NW = D / 16, RT = D / 16, KB = D / 32;
   constexpr int SHARE = S::OPS / NW;  // fewest stage loads of one wave per chunk
   extern __shared__ __align__(16) unsigned char lds[];
@@ -545,7 +529,6 @@ __global__ __launch_bounds__(64 * (D / 16), 1) void seg_pair_kernel(PrefillArgs 
     const T *__restrict__ Bg = static_cast<const T *>(a.Bc);
     struct Lane {
       uint2 b[RT];  // B rows 16rt + 4grp .. +3 of tile w
-      float dec;    // GDN decay of the chunk
     };
     auto fetch = [&](Lane &op, int c) {
       const size_t bk = blk(c);
@@ -556,7 +539,6 @@ __global__ __launch_bounds__(64 * (D / 16), 1) void seg_pair_kernel(PrefillArgs 
         op.b[2 * i] = make_uint2(v[0], v[1]);
         op.b[2 * i + 1] = make_uint2(v[2], v[3]);
       }
-      if constexpr (!KDA) op.dec = a.dec[bk * D];
     };
     Lane ring[2];
     fetch(ring[0], 0);
@@ -587,12 +569,7 @@ __global__ __launch_bounds__(64 * (D / 16), 1) void seg_pair_kernel(PrefillArgs 
       }
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        f32x4 d;
-        if constexpr (KDA) {
-          d = *reinterpret_cast<const f32x4 *>(stl - lane * 16 + S::NM_BYTES + (16 * rt + 4 * grp) * 4);
-        } else {
-          d = f32x4{ring[u].dec, ring[u].dec, ring[u].dec, ring[u].dec};
-        }
+        const f32x4 d = *reinterpret_cast<const f32x4 *>(stl - lane * 16 + S::NM_BYTES + (16 * rt + 4 * grp) * 4);
         HA[rt] = d * HA[rt];
         HB[rt] = d * HB[rt] + raw4_to_f32(ring[u].b[rt]);
       }
@@ -662,12 +639,12 @@ __global__ __launch_bounds__(64 * (D / 16), 1) void seg_pair_kernel(PrefillArgs 
   }
 }
 
-template <typename T, int D, bool KDA, bool SINGLE>
+template <typename T, int D, bool SINGLE>
 static hipError_t launch_pair_t(const PrefillArgs &a, hipStream_t stream) {
-  using S = WalkStage<T, D, KDA, false>;
+  using S = WalkStage<T, D, false>;
   constexpr int kMaxDevices = 64;
   static std::atomic<bool> done[kMaxDevices];
-  const void *kern = reinterpret_cast<const void *>(&seg_pair_kernel<T, D, KDA, SINGLE>);
+  const void *kern = reinterpret_cast<const void *>(&seg_pair_kernel<T, D, SINGLE>);
   constexpr int walk_lds = S::NSTAGE * S::BYTES;
   constexpr int tr_lds = D * (D + 8) * (int)sizeof(T);
   const int lds = walk_lds > tr_lds ? walk_lds : tr_lds;
@@ -679,17 +656,17 @@ static hipError_t launch_pair_t(const PrefillArgs &a, hipStream_t stream) {
     if (dev >= 0 && dev < kMaxDevices) done[dev].store(true, std::memory_order_relaxed);
   }
   const long blocks = (long)a.max_segs * a.Hv;
-  hipLaunchKernelGGL((seg_pair_kernel<T, D, KDA, SINGLE>), dim3((unsigned)blocks), dim3(64 * (D / 16)), lds, stream,
+  hipLaunchKernelGGL((seg_pair_kernel<T, D, SINGLE>), dim3((unsigned)blocks), dim3(64 * (D / 16)), lds, stream,
                      a);
   return hipGetLastError();
 }
 
-template <typename T, int DK, int DV, bool KDA, bool SINGLE, int TPW>
+template <typename T, int DK, int DV, bool SINGLE, int TPW>
 static hipError_t launch_maps_t(const PrefillArgs &a, hipStream_t stream) {
-  using S = WalkStage<T, DK, KDA, false>;
+  using S = WalkStage<T, DK, false>;
   constexpr int kMaxDevices = 64;
   static std::atomic<bool> done[kMaxDevices];
-  const void *kern = reinterpret_cast<const void *>(&seg_map_kernel<T, DK, DV, KDA, SINGLE, TPW>);
+  const void *kern = reinterpret_cast<const void *>(&seg_map_kernel<T, DK, DV, SINGLE, TPW>);
   constexpr int walk_lds = S::NSTAGE * S::BYTES;
   constexpr int tr_lds = DK * (16 * TPW + 8) * (int)sizeof(T);
   const int lds = walk_lds > tr_lds ? walk_lds : tr_lds;
@@ -703,37 +680,36 @@ static hipError_t launch_maps_t(const PrefillArgs &a, hipStream_t stream) {
   const long items = (long)a.max_segs * a.Hv;
   const long groups = (items + kXcds - 1) / kXcds;
   const long blocks = groups * kXcds * (DK / (16 * TPW) + DV / (16 * TPW));
-  hipLaunchKernelGGL((seg_map_kernel<T, DK, DV, KDA, SINGLE, TPW>), dim3((unsigned)blocks), dim3(64 * (TPW + 1)), lds,
+  hipLaunchKernelGGL((seg_map_kernel<T, DK, DV, SINGLE, TPW>), dim3((unsigned)blocks), dim3(64 * (TPW + 1)), lds,
                      stream, a);
   return hipGetLastError();
 }
 
-template <int DK, int DV, bool KDA>
+template <int DK, int DV>
 hipError_t launch_maps_dims(const PrefillArgs &a, hipStream_t s) {
   if constexpr (DK == DV)
-    return a.single ? launch_pair_t<bf16_t, DK, KDA, true>(a, s) : launch_pair_t<bf16_t, DK, KDA, false>(a, s);
+    return a.single ? launch_pair_t<bf16_t, DK, true>(a, s) : launch_pair_t<bf16_t, DK, false>(a, s);
   // as many tiles per workgroup as the narrower map has: fewer copies of each NM block
   constexpr int TPW = (DK < DV ? DK : DV) / 16;
-  return a.single ? launch_maps_t<bf16_t, DK, DV, KDA, true, TPW>(a, s)
-                  : launch_maps_t<bf16_t, DK, DV, KDA, false, TPW>(a, s);
+  return a.single ? launch_maps_t<bf16_t, DK, DV, true, TPW>(a, s)
+                  : launch_maps_t<bf16_t, DK, DV, false, TPW>(a, s);
 }
 
-template <bool KDA>
-hipError_t launch_maps_kind(const PrefillArgs &a, hipStream_t s) {
-  if (a.Dk == 64 && a.Dv == 64) return launch_maps_dims<64, 64, KDA>(a, s);
-  if (a.Dk == 64 && a.Dv == 128) return launch_maps_dims<64, 128, KDA>(a, s);
-  if (a.Dk == 128 && a.Dv == 64) return launch_maps_dims<128, 64, KDA>(a, s);
-  return launch_maps_dims<128, 128, KDA>(a, s);
+hipError_t launch_maps_all(const PrefillArgs &a, hipStream_t s) {
+  if (a.Dk == 64 && a.Dv == 64) return launch_maps_dims<64, 64>(a, s);
+  if (a.Dk == 64 && a.Dv == 128) return launch_maps_dims<64, 128>(a, s);
+  if (a.Dk == 128 && a.Dv == 64) return launch_maps_dims<128, 64>(a, s);
+  return launch_maps_dims<128, 128>(a, s);
 }
 
 // The staged walk's LDS (three stages) exceeds the default 64 KiB limit: raise
 // it once per device and instance.
-template <typename T, int DK, int DV, bool KDA, bool SINGLE, int TPW>
+template <typename T, int DK, int DV, bool SINGLE, int TPW>
 static hipError_t launch_walk_t(const PrefillArgs &a, long groups, hipStream_t stream) {
-  using S = WalkStage<T, DK, KDA>;
+  using S = WalkStage<T, DK>;
   constexpr int kMaxDevices = 64;
   static std::atomic<bool> done[kMaxDevices];
-  const void *kern = reinterpret_cast<const void *>(&state_walk_kernel<T, DK, DV, KDA, SINGLE, TPW>);
+  const void *kern = reinterpret_cast<const void *>(&state_walk_kernel<T, DK, DV, SINGLE, TPW>);
   const int lds = S::NSTAGE * S::BYTES;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -743,44 +719,39 @@ static hipError_t launch_walk_t(const PrefillArgs &a, long groups, hipStream_t s
     if (dev >= 0 && dev < kMaxDevices) done[dev].store(true, std::memory_order_relaxed);
   }
   const long blocks = groups * kXcds * (DV / (16 * TPW));
-  hipLaunchKernelGGL((state_walk_kernel<T, DK, DV, KDA, SINGLE, TPW>), dim3((unsigned)blocks), dim3(64 * (TPW + 1)),
+  hipLaunchKernelGGL((state_walk_kernel<T, DK, DV, SINGLE, TPW>), dim3((unsigned)blocks), dim3(64 * (TPW + 1)),
                      lds, stream, a);
   return hipGetLastError();
 }
 
-template <typename T, int DK, int DV, bool KDA, int TPW>
+template <typename T, int DK, int DV, int TPW>
 static hipError_t launch_walk_single(const PrefillArgs &a, long groups, hipStream_t stream) {
-  return a.single ? launch_walk_t<T, DK, DV, KDA, true, TPW>(a, groups, stream)
-                  : launch_walk_t<T, DK, DV, KDA, false, TPW>(a, groups, stream);
+  return a.single ? launch_walk_t<T, DK, DV, true, TPW>(a, groups, stream)
+                  : launch_walk_t<T, DK, DV, false, TPW>(a, groups, stream);
 }
 
-template <int DK, int DV, bool KDA>
+template <int DK, int DV>
 hipError_t launch_walk_dims(const PrefillArgs &a, int cus, hipStream_t stream) {
   const long pairs = (long)a.N * a.Hv;
   const long groups = (pairs + kXcds - 1) / kXcds;
   const long blocks = groups * kXcds * (DV / 16);
   // tiles of a head share a workgroup and its stages: two while that fits
   // the CUs in one round, else four
-  if (blocks <= 2L * cus) return launch_walk_single<bf16_t, DK, DV, KDA, 2>(a, groups, stream);
-  return launch_walk_single<bf16_t, DK, DV, KDA, 4>(a, groups, stream);
+  if (blocks <= 2L * cus) return launch_walk_single<bf16_t, DK, DV, 2>(a, groups, stream);
+  return launch_walk_single<bf16_t, DK, DV, 4>(a, groups, stream);
 }
 
-template <bool KDA>
-hipError_t launch_walk_kind(const PrefillArgs &a, int cus, hipStream_t s) {
-  if (a.Dk == 64 && a.Dv == 64) return launch_walk_dims<64, 64, KDA>(a, cus, s);
-  if (a.Dk == 64 && a.Dv == 128) return launch_walk_dims<64, 128, KDA>(a, cus, s);
-  if (a.Dk == 128 && a.Dv == 64) return launch_walk_dims<128, 64, KDA>(a, cus, s);
-  return launch_walk_dims<128, 128, KDA>(a, cus, s);
+hipError_t launch_walk_all(const PrefillArgs &a, int cus, hipStream_t s) {
+  if (a.Dk == 64 && a.Dv == 64) return launch_walk_dims<64, 64>(a, cus, s);
+  if (a.Dk == 64 && a.Dv == 128) return launch_walk_dims<64, 128>(a, cus, s);
+  if (a.Dk == 128 && a.Dv == 64) return launch_walk_dims<128, 64>(a, cus, s);
+  return launch_walk_dims<128, 128>(a, cus, s);
 }
 
 }  // namespace
 
-hipError_t launch_seg_maps(const PrefillArgs &a, bool kda, hipStream_t s) {
-  return kda ? launch_maps_kind<true>(a, s) : launch_maps_kind<false>(a, s);
-}
+hipError_t launch_seg_maps(const PrefillArgs &a, hipStream_t s) { return launch_maps_all(a, s); }
 
-hipError_t launch_state_walk(const PrefillArgs &a, bool kda, int cus, hipStream_t s) {
-  return kda ? launch_walk_kind<true>(a, cus, s) : launch_walk_kind<false>(a, cus, s);
-}
+hipError_t launch_state_walk(const PrefillArgs &a, int cus, hipStream_t s) { return launch_walk_all(a, cus, s); }
 
 }  // namespace hagdn

@@ -688,12 +688,12 @@ static hipError_t dispatch_dims(const PrefillArgs &a, hipStream_t s) {
 
 template <bool TRANSFER>
 static hipError_t dispatch(const PrefillArgs &a, bool bf16, bool kda, hipStream_t s) {
-  if (bf16) return kda ? dispatch_dims<bf16_t, true, TRANSFER>(a, s) : dispatch_dims<bf16_t, false, TRANSFER>(a, s);
+  if (bf16) return dispatch_dims<bf16_t, true, TRANSFER>(a, s);  // KDA: GDN segments take the compact path
   return kda ? dispatch_dims<float, true, TRANSFER>(a, s) : dispatch_dims<float, false, TRANSFER>(a, s);
 }
 
 hipError_t launch_seg_transfer(const PrefillArgs &a, bool bf16, bool kda, hipStream_t s) {
-  if (bf16) return launch_seg_maps(a, kda, s);
+  if (bf16) return launch_seg_maps(a, s);
   return kda ? dispatch_dims<float, true, true>(a, s) : dispatch_dims<float, false, true>(a, s);
 }
 

@@ -195,11 +195,11 @@ inline bool overlap_supported(bool bf16, bool kda, int Dk, int Dv) {
 hipError_t launch_overlap_setup(const PrefillArgs &a, hipStream_t stream);
 // Chunk-local items and whole-chain walks in one launch (k1_chunk_local.hip).
 hipError_t launch_overlapped(const PrefillArgs &a, hipStream_t stream);
-// the bf16 whole-chain walk for batches with more walks than the device's
+// KDA's bf16 whole-chain walk for batches with more walks than the device's
 // compute units (a.cus; k2_walk.hip)
-hipError_t launch_state_walk(const PrefillArgs &a, bool kda, int cus, hipStream_t stream);
-// the bf16 segment maps on the staged walk (k2_walk.hip)
-hipError_t launch_seg_maps(const PrefillArgs &a, bool kda, hipStream_t stream);
+hipError_t launch_state_walk(const PrefillArgs &a, int cus, hipStream_t stream);
+// KDA's bf16 segment maps on the staged walk (k2_walk.hip)
+hipError_t launch_seg_maps(const PrefillArgs &a, hipStream_t stream);
 // the compact path (compact.h, GDN in bf16): its chunk-local kernel, its
 // whole-chain walk, and its segment maps and per-segment walks
 hipError_t launch_chunk_compact(const PrefillArgs &a, hipStream_t stream);

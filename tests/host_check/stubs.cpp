@@ -10,8 +10,8 @@ hipError_t launch_chunk_local(const PrefillArgs &, bool, bool, hipStream_t) { re
 hipError_t launch_state_prop(const PrefillArgs &, bool, bool, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_overlap_setup(const PrefillArgs &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_overlapped(const PrefillArgs &, hipStream_t) { return hipErrorNoDevice; }
-hipError_t launch_state_walk(const PrefillArgs &, bool, int, hipStream_t) { return hipErrorNoDevice; }
-hipError_t launch_seg_maps(const PrefillArgs &, bool, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_state_walk(const PrefillArgs &, int, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_seg_maps(const PrefillArgs &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_chunk_compact(const PrefillArgs &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_compact_walk(const PrefillArgs &, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_compact_maps(const PrefillArgs &, hipStream_t) { return hipErrorNoDevice; }
