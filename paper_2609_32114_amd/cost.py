@@ -38,7 +38,8 @@ def algorithmic_bytes(T_total: int, N: int, Hqk: int, Hv: int, dk: int, dv: int,
 
 
 def kernel_bytes(kernel: str, T_total: int, N: int, Hqk: int, Hv: int, dk: int, dv: int,
-                 elt_bytes: int, kda: bool, with_s0: bool, chunk: int = 64, seg_chunks: int = 0) -> int:
+                 elt_bytes: int, kda: bool, with_s0: bool, chunk: int = 64, seg_chunks: int = 0,
+                 compact: bool = False) -> int:
     """Compulsory bytes of one kernel of the pipeline: every input it reads and
     every output it writes, each counted once.  Per-chunk blocks are counted per
     (chunk, value head); the timed workloads are single sequences with
@@ -52,6 +53,11 @@ def kernel_bytes(kernel: str, T_total: int, N: int, Hqk: int, Hv: int, dk: int, 
                     the segment maps A (dk x dk) and B_seg (dk x dv fp32) out
       state_prop    -M, B, decay, Q', O_loc, the segment maps and s0 in; o, s_final
                     out (operators #5 and #6)
+      compact calls (csrc/compact.h): chunk_local reads q, k, gate, beta and
+                    writes 13 KiB per block; seg_transfer (maps and their scan)
+                    reads k, v and 7 KiB per block and, per map in between, reads
+                    A and B_seg and writes the entering state; state_prop reads
+                    q, k, v, the 13 KiB and the entering states
       overlap_setup the overlapped launch's queues (2 KiB) and ready flags cleared
       overlapped    chunk_local and state_prop in one launch: q, k, v, gate, beta
                     and s0 in, o and s_final out; the factors pass between its
@@ -69,6 +75,16 @@ def kernel_bytes(kernel: str, T_total: int, N: int, Hqk: int, Hv: int, dk: int, 
     maps = (segs - 1) * Hv * (dk * dk * e + dk * dv * 4)
     if kernel == "chunk_index":
         return (N + 1) * 4 + N * 16 + (T_total // chunk + N) * 16 + 4 + N * 8 + (chunks // L + N) * 16
+    if compact and kernel in ("chunk_local", "seg_transfer", "state_prop"):
+        tri, vec = 6 * 1024, 1024
+        key, val = 2 * Hqk * dk, 2 * Hv * dv  # bytes per token
+        if kernel == "chunk_local":
+            return T_total * (2 * key + 8 * Hv) + cb * (2 * tri + vec)
+        if kernel == "seg_transfer":
+            scan = max(0, segs - 2) * Hv * (dk * dk * 2 + 8 * dk * dv)
+            return map_chunks * (chunk * (key + val) + Hv * (tri + vec)) + maps + scan
+        rd = T_total * (2 * key + val) + cb * (2 * tri + vec) + (segs - 1) * Hv * dk * dv * 4
+        return rd + (state if with_s0 else 0) + T_total * val + state
     if kernel == "chunk_local":
         rd = T_total * (2 * Hqk * dk * e + Hv * dv * e + gate + Hv * 4)
         wr = cb * ((dk * dk + dk * dv + chunk * dk + chunk * dv) * e + decb)
