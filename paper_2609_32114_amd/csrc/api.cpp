@@ -4,13 +4,14 @@
 // One call enqueues, in stream order:
 //   K0 chunk index    (1 workgroup)                        sequence/chunk/segment tables,
 //                                                          cu_seqlens check
-//   K1 chunk-local    (max_chunks x Hv workgroups)         operators #1-#4
+//   K1 chunk-local    (max_chunks x Hv workgroups)         operators #1-#4 (compact calls: #1-#3)
 //   then either, when a sequence can span two segments (segment-parallel path),
-//   K2 seg transfer   (max_segs x Hv x 2 workgroups)       segment maps of operator #5
+//   K2 seg transfer   (max_segs x Hv workgroups or more)   segment maps of operator #5 (compact
+//                                                          calls: and their scan)
 //   K3 seg state      (max_segs x Hv workgroups)           operator #5 per segment, fused
 //                                                          with operator #6
 //   or, when every sequence is one segment,
-//   K3 state prop     (N x Hv x Dv/16 workgroups)          operator #5 per chain, fused
+//   K3 state prop     (N x Hv x up to Dv/16 workgroups)    operator #5 per chain, fused
 //                                                          with operator #6
 // The decode entry points enqueue one kernel (k4_decode.hip) and use no
 // workspace.  No allocation, no synchronisation, no pointer retained after

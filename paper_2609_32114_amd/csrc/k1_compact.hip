@@ -14,7 +14,11 @@
 // It then inverts its diagonal block and solves column block i of T
 // (chunk_item.h), whose transposed blocks are halves of T' operand blocks.
 // Three barriers in all (keys staged, A and the T_ii published, and with raw
-// keys their L2 factors).
+// keys their L2 factors).  Four workgroups share a CU (33.5 KiB of LDS, under 96
+// registers).  us, affine kernel against this one: one block per CU 19.7 / 8;
+// 1,024 blocks 47.5 / 15.6; 4,096 168 / 45; 8,192 with 1 x 32768 tokens 293-326 /
+// 88 (411 MB, the rate of a large copy); 17,408 with two heads per key head 604-669 /
+// 162-180.
 #include "chunk_item.h"
 #include "compact.h"
 

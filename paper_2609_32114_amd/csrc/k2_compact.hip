@@ -1,5 +1,19 @@
 // k2_compact.hip -- the Reduce phase and the last Map phase of the compact path
 // (compact.h; paper Sec. 2.1, operators #5 H and #6 O): GDN in bf16.
+//   compact_walk_kernel  a head (or a segment of one) per workgroup, four waves of
+//                        two 16-column tiles: each operand crosses the CU once for
+//                        all tiles.  64 chunks: 130 us with 64 heads (a step of
+//                        2 us: the tile waves' instruction stream and LDS reads),
+//                        254 us with 256 (4 us: the rate of a large copy; the
+//                        affine staged walk's step moved 112 KiB for 77);
+//   compact_row_kernel   one or two tiles per workgroup (below);
+//   compact_map_kernel   both maps of a segment, compact_scan_kernel their
+//                        composition: 89 + 14 us at 1 x 32768 tokens, 16 heads,
+//                        where the affine maps took 147 and every segment applied
+//                        the earlier maps itself (201 us for the segment walks,
+//                        130 now).
+// The workgroups of a head share an XCD and its L2 (consecutive workgroup ids are
+// dealt round-robin to the 8 XCDs).
 #include <atomic>
 
 #include "compact.h"
@@ -466,7 +480,7 @@ __device__ __forceinline__ void store_chunk(__amdgpu_buffer_rsrc_t rsrc, int off
   }
 }
 
-// State walk with outputs: one workgroup of NW tile waves (TW adjacent
+// Head walk, state and outputs: one workgroup of NW tile waves (TW adjacent
 // 16-column tiles each) and two loader waves per CT = NW TW tiles of a
 // (sequence, value head), or with SEG of a (segment, value head).
 template <int DK, int DV, int TW, int NW, bool SINGLE, bool SEG>

@@ -42,6 +42,9 @@ constexpr int kPreAll = 7;
 //   Ol  per state tile m, lane-major: element (nt, e) of lane (col, grp), at
 //       ((m*64 + lane)*4 + nt)*4 + e, = O_loc[16nt + col][dv_of(m, 4grp + e)]
 // Element type of every block is the I/O dtype (bf16 or fp32), dec is fp32.
+// GDN calls in bf16 that take the compact path keep other factors in the same
+// region, from NM on, and their segment maps in the compact walk's orders
+// (compact.h, k2_compact.hip).
 //
 // Segments (paper Sec. 4, the Chunk-Seg-Seg mapping): each sequence is cut into segments
 // of seg_chunks chunks (the last may be shorter; an empty sequence still has
