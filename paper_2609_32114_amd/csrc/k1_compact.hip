@@ -13,12 +13,14 @@
 // lane column), so the P accumulators are P' operand fragments as they stand.
 // It then inverts its diagonal block and solves column block i of T
 // (chunk_item.h), whose transposed blocks are halves of T' operand blocks.
-// Three barriers in all (keys staged, A and the T_ii published, and with raw
-// keys their L2 factors).  Four workgroups share a CU (33.5 KiB of LDS, under 96
-// registers).  us, affine kernel against this one: one block per CU 19.7 / 8;
-// 1,024 blocks 47.5 / 15.6; 4,096 168 / 45; 8,192 with 1 x 32768 tokens 293-326 /
-// 88 (411 MB, the rate of a large copy); 17,408 with two heads per key head 604-669 /
-// 162-180.
+// Four barriers in all (keys staged, and free again, A and the T_ii published,
+// and with raw keys their L2 factors).  A takes the keys' place in LDS, so five
+// workgroups share a CU (17.5 KiB of LDS, under 96 registers); in a place of its
+// own, at four per CU and one barrier less, the last three calls below took 162-183,
+// 44 and 90.  us, affine kernel against this one: one block per CU 19.7 / 8; 1,024
+// blocks 47.5 / 15.6; 17,408 with two heads per key head 604-669 / 148-167; 3,200
+// raw ones 134-145 / 42; 8,192 with 1 x 32768 tokens 293-326 / 76-87 (411 MB, the
+// rate of a large copy).  Six per CU spill.
 #include "chunk_item.h"
 #include "compact.h"
 
@@ -28,12 +30,15 @@ namespace {
 constexpr int kThreads = 256;
 
 template <int DK, bool PRE>
-__global__ __launch_bounds__(kThreads, 4) void chunk_compact_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(kThreads, 5) void chunk_compact_kernel(PrefillArgs a) {
   constexpr int KB = DK / 32, ROW = DK * 2, PIECES = ROW / 16;
   constexpr int RPB = 1024 / ROW;       // rows of one 1 KiB load
   constexpr int LPW = kChunk / RPB / 4; // loads per wave
-  __shared__ __align__(16) unsigned char sK[kChunk * ROW];
-  __shared__ __align__(16) float sA[kChunk * kChunk];  // strictly lower blocks: A; diagonal blocks: T_ii
+  // keys until op #2 is done with them, then A (strictly lower blocks) and T_ii
+  // (diagonal blocks): 17.5 KiB a workgroup, so five share a CU
+  constexpr int kTile = kChunk * ROW > kChunk * kChunk * 4 ? kChunk * ROW : kChunk * kChunk * 4;
+  __shared__ __align__(16) unsigned char sK[kTile];
+  float *sA = reinterpret_cast<float *>(sK);
   __shared__ double sGam[kChunk];
   __shared__ __align__(16) float sBeta[kChunk], sNk[kChunk];
   const LocalItem cur = local_item(a, blockIdx.x);
@@ -133,9 +138,13 @@ __global__ __launch_bounds__(kThreads, 4) void chunk_compact_kernel(PrefillArgs 
         accA[j][e] = (s < r && r < len) ? br * accA[j][e] * dec : 0.f;
         accP[j][e] = s <= r ? accP[j][e] * dec * (a.scale * nq) : 0.f;
       }
-      if (j < wave) *reinterpret_cast<f32x4 *>(sA + swz<float, kChunk>(r, 16 * j + 4 * grp)) = accA[j];
     }
   }
+
+  __syncthreads();  // every wave is done with the keys
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    if (j < wave) *reinterpret_cast<f32x4 *>(sA + swz<float, kChunk>(r, 16 * j + 4 * grp)) = accA[j];
 
   // ---- op #3, diagonal block: column `col` of (I + A_ii)^-1 by forward
   //      substitution; A_ii[x][y] sits in lane x + 16 (y / 4), element y % 4
