@@ -63,12 +63,12 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 def kernel_source_hash(name: str) -> str:
     """Hash of the sources a kernel is built from (traffic counters go stale when they change)."""
     csrc = os.path.join(ROOT, "paper_2609_32114_amd", "csrc")
-    item = ("k1_chunk_local.hip", "chunk_item.h", "state_walk.h")
+    item = ("k1_chunk_local.hip", "chunk_item.h", "gate_map.h", "state_walk.h")
     compact = ("compact.h", "k2_compact.hip")
     files = {"chunk_local": item + ("k1_compact.hip", "compact.h"),
              "state_prop": ("k2_state_prop.hip", "state_walk.h", "k2_walk.hip", "k3_segments.hip") + compact,
              "seg_transfer": ("k3_segments.hip", "k2_walk.hip") + compact, "chunk_index": ("k0_chunk_index.hip",),
-             "decode": ("k4_decode.hip",),
+             "decode": ("k4_decode.hip", "gate_map.h"),
              "overlap_setup": ("k1_chunk_local.hip",),
              "overlapped": item}
     h = hashlib.sha256()

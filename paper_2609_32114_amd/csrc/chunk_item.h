@@ -3,6 +3,7 @@
 #pragma once
 
 #include "device.h"
+#include "gate_map.h"
 #include "prefill.h"
 
 namespace hagdn {

@@ -246,30 +246,6 @@ __device__ __forceinline__ f32x4 mma(f32x4 acc, f32x8 a, f32x8 b) {
 }
 
 // ------------------------------------------------ input preprocessing maps
-// Raw projection -> log-gate: -softplus(x) = -(max(x, 0) + log1p(e^-|x|)), the
-// form in which the exponential cannot overflow.  log1p(e) = 2 atanh(s), s = e /
-// (2 + e) <= 1/3, by its Taylor series to s^15 (the next term is below 2^-25 of
-// the sum); e by the hardware's exp2 of the rounded product with the product's
-// remainder applied to first order.  Within 4 ulp of softplus in fp32.  KDA maps
-// a gate per channel: the library's log1p and exp took a third of a raw item's
-// vector instructions.
-__device__ __forceinline__ float neg_softplus(float x) {
-  const float a = -fabsf(x);
-  constexpr float kLog2e = 1.44269504088896340736f, kLog2eLo = 1.92596298909109e-8f, kLn2 = 0.693147180559945309f;
-  float t = a * kLog2e;
-  t = t < -150.f ? -150.f : t;  // e^a = 0 there, with no remainder (a selection: NaN stays NaN)
-  const float lo = t > -150.f ? fmaf(a, kLog2e, -t) + a * kLog2eLo : 0.f;
-  float e = __builtin_amdgcn_exp2f(t);
-  e = fmaf(e * kLn2, lo, e);
-  const float s = e * __builtin_amdgcn_rcpf(2.f + e), z = s * s;
-  float p = fmaf(z, 2.f / 15.f, 2.f / 13.f);
-  p = fmaf(z, p, 2.f / 11.f);
-  p = fmaf(z, p, 2.f / 9.f);
-  p = fmaf(z, p, 2.f / 7.f);
-  p = fmaf(z, p, 2.f / 5.f);
-  p = fmaf(z, p, 2.f / 3.f);
-  return -(fmaxf(x, 0.f) + fmaf(s * z, p, 2.f * s));
-}
 // Raw projection -> write strength in (0, 1).
 __device__ __forceinline__ float sigmoid(float x) { return 1.f / (1.f + expf(-x)); }
 // Factor that L2-normalises a vector with squared norm ss (norm floored at 1e-6).

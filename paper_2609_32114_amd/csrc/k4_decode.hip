@@ -17,6 +17,7 @@
 // touched once per step, and keeping them out of the caches measured faster
 // once the pool outgrows the Infinity Cache (0.96x the time at 256 MiB).
 #include "device.h"
+#include "gate_map.h"
 #include "prefill.h"
 
 namespace hagdn {
