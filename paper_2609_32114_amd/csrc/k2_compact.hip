@@ -199,20 +199,19 @@ __device__ __forceinline__ void load_chunks(const PrefillArgs &a, const Span &sp
   }
 }
 
-// The state of TW adjacent column tiles of one head in one wave, and one
+// The state of two adjacent column tiles of one head in one wave, and one
 // chunk step of it: H[t][rt][e] = S^T[dk_of(rt, 4grp + e)][dv_of(tile0 + t, col)].
 // VALUES: the tiles take the chunks' value terms (the map of a state alone
 // does not).
-template <int DK, int DV, int CT, int TW, bool OUT, bool VALUES>
+template <int DK, int DV, int CT, bool OUT, bool VALUES>
 struct TileWalk {
   using S = Stage<DK, CT, OUT>;
-  static constexpr int RT = DK / 16, KB = DK / 32;
+  static constexpr int TW = 2, RT = DK / 16, KB = DK / 32;
   f32x4 H[TW][RT];
   int lane, col, grp;
   int koff[KB];      // natural key / query operand: row col, piece 4kb + grp
   int ktoff[KB];     // transposed key operand: row 4grp + col / 4, piece 4 (rt / 2) + col % 4
   int voff;          // transposed value tile pair of this wave (first tile of the pair)
-  int vhalf;         // TW = 1: which tile of the pair
 
   __device__ __forceinline__ void init(int tile_in_wg) {
     lane = threadIdx.x & 63;
@@ -225,7 +224,6 @@ struct TileWalk {
       ktoff[kb] = tr * S::KROW + (((4 * kb + (col & 3)) ^ row_swz<S::KROW>(tr)) << 4);
     }
     voff = tr * S::VROW + (((4 * (tile_in_wg >> 1) + (col & 3)) ^ row_swz<S::VROW>(tr)) << 4);
-    vhalf = TW == 1 ? 8 * (tile_in_wg & 1) : 0;
   }
 
   // Operand groups of one chunk, in the order the step consumes them: four K
@@ -284,7 +282,7 @@ struct TileWalk {
   // O^T[t][nt], token 16nt + col, columns dv_of(tile0 + t, 4grp .. +3).
   template <typename Store>
   __device__ __forceinline__ void step(const unsigned char *lds, int c, Store store) {
-    const unsigned char *stv = st + S::off_v + voff + vhalf;
+    const unsigned char *stv = st + S::off_v + voff;
     const float *vec = reinterpret_cast<const float *>(sb + S::off_vec);
     int cur = 0;
     f32x4 o[TW][4];
@@ -464,34 +462,24 @@ struct TileWalk {
   }
 };
 
-// The outputs of one chunk, rows from `row0` of the resource: tokens
-// 16nt + col, TW tiles' columns (eight consecutive ones for a tile pair).
-template <int TW>
-__device__ __forceinline__ void store_chunk(__amdgpu_buffer_rsrc_t rsrc, int off, int step, const f32x4 (&o)[TW][4]) {
+// The outputs of one chunk: tokens 16nt + col, the tile pair's eight consecutive
+// columns.
+__device__ __forceinline__ void store_chunk(__amdgpu_buffer_rsrc_t rsrc, int off, int step, const f32x4 (&o)[2][4]) {
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    if constexpr (TW == 2) {
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, frag_from_acc<bf16_t>(o[0][nt], o[1][nt])), rsrc,
-                                             off + nt * step, 0, 0);
-    } else {
-      const bf16x4 v = __builtin_convertvector(o[0][nt], bf16x4);
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rsrc, off + nt * step, 0, 0);
-    }
-  }
+  for (int nt = 0; nt < 4; ++nt)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, frag_from_acc<bf16_t>(o[0][nt], o[1][nt])), rsrc,
+                                           off + nt * step, 0, 0);
 }
 
-// Head walk, state and outputs: one workgroup of NW tile waves (TW adjacent
-// 16-column tiles each) and two loader waves per CT = NW TW tiles of a
-// (sequence, value head), or with SEG of a (segment, value head).
-template <int DK, int DV, int TW, int NW, bool SINGLE, bool SEG>
-__global__ __launch_bounds__(64 * (NW + 2), 1) void compact_walk_kernel(PrefillArgs a) {
-  constexpr int CT = TW * NW, NG = DV / (16 * CT), RT = DK / 16;
+// Head walk, state and outputs: one workgroup of d_v / 32 tile waves (two
+// adjacent 16-column tiles each) and two loader waves per (sequence, value
+// head), or with SEG per (segment, value head).
+template <int DK, int DV, bool SINGLE, bool SEG>
+__global__ __launch_bounds__(64 * (DV / 32 + 2), 1) void compact_walk_kernel(PrefillArgs a) {
+  constexpr int TW = 2, NW = DV / 32, CT = DV / 16, RT = DK / 16;
   extern __shared__ __align__(16) unsigned char lds[];
   single_status<SINGLE>(a);
-  const int b = blockIdx.x;
-  const int pair = (b / kXcds / NG) * kXcds + b % kXcds;  // the workgroups of a head share an XCD
-  const int tg = (b / kXcds) % NG;
-  if (pair >= (SEG ? a.max_segs : a.N) * a.Hv) return;  // uniform for the workgroup
+  const int pair = blockIdx.x;
   const int s = pair / a.Hv, h = pair % a.Hv;           // sequence or segment, value head
   int4 sg = {s, 0, 0, 0};  // {sequence, first chunk, chunks, index in sequence}
   if constexpr (SEG) sg = seg_info_at<SINGLE>(a, s);
@@ -504,15 +492,14 @@ __global__ __launch_bounds__(64 * (NW + 2), 1) void compact_walk_kernel(PrefillA
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 
   if (wave >= NW) {
-    // first of the staged value columns: the workgroup's tiles, or their pair
-    load_chunks<DK, DV, CT, true>(a, sp, h, CT == 1 ? 32 * (tg >> 1) : 16 * CT * tg, lds, wave - NW, lane);
+    load_chunks<DK, DV, CT, true>(a, sp, h, 0, lds, wave - NW, lane);
     return;
   }
 
   // ---- tile wave
-  const int tile0 = tg * CT + wave * TW;
-  TileWalk<DK, DV, CT, TW, true, true> w;
-  w.init(CT == 1 ? (tile0 & 1) : wave * TW);
+  const int tile0 = wave * TW;
+  TileWalk<DK, DV, CT, true, true> w;
+  w.init(tile0);
   const int col = w.col, grp = w.grp;
   const size_t sbase = ((size_t)n * a.Hv + h) * DK * DV;
   if (SEG && sg.w > 0) {
@@ -541,7 +528,7 @@ __global__ __launch_bounds__(64 * (NW + 2), 1) void compact_walk_kernel(PrefillA
     const int orow = (col * a.Hv + h) * DV * 2 + dv_of(tile0, 4 * grp) * 2, ostep = 16 * (int)row_bytes;
     w.begin(lds);
     for (int c = 0; c < sp.nch; ++c) {
-      w.step(lds, c, [&](const f32x4(&o)[TW][4]) { store_chunk<TW>(orsrc, orow + 4 * c * ostep, ostep, o); });
+      w.step(lds, c, [&](const f32x4(&o)[TW][4]) { store_chunk(orsrc, orow + 4 * c * ostep, ostep, o); });
     }
   }
   if (a.s_final && sg.w == ss.y - 1) {
@@ -808,7 +795,7 @@ __device__ __forceinline__ void map_tiles(const PrefillArgs &a, int s, int h, in
   constexpr int RT = DK / 16, KB = DK / 32, NT = DV / 16;
   const int lane = threadIdx.x & 63;
   const int nch = sg.z;
-  TileWalk<DK, DV, NT, 2, false, !APART> w;
+  TileWalk<DK, DV, NT, false, !APART> w;
   w.init(APART ? 0 : wave * 2);
   const int col = w.col, grp = w.grp;
   const bool from_s0 = !APART && sg.w == 0 && a.s0;
@@ -962,17 +949,16 @@ hipError_t raise_lds(const void *kern, int lds, std::atomic<bool> (&done)[kMaxDe
   return hipSuccess;
 }
 
-template <int DK, int DV, int TW, int NW, bool SINGLE, bool SEG>
+template <int DK, int DV, bool SINGLE, bool SEG>
 hipError_t launch_walk_t(const PrefillArgs &a, hipStream_t stream) {
-  constexpr int lds = Stage<DK, TW * NW, true>::BYTES;
-  const void *kern = reinterpret_cast<const void *>(&compact_walk_kernel<DK, DV, TW, NW, SINGLE, SEG>);
+  constexpr int lds = Stage<DK, DV / 16, true>::BYTES;
+  const void *kern = reinterpret_cast<const void *>(&compact_walk_kernel<DK, DV, SINGLE, SEG>);
   static std::atomic<bool> done[kMaxDevices];
   hipError_t e = raise_lds(kern, lds, done);
   if (e != hipSuccess) return e;
-  const long groups = ((long)(SEG ? a.max_segs : a.N) * a.Hv + kXcds - 1) / kXcds;
-  const long blocks = groups * kXcds * (DV / (16 * TW * NW));
-  hipLaunchKernelGGL((compact_walk_kernel<DK, DV, TW, NW, SINGLE, SEG>), dim3((unsigned)blocks), dim3(64 * (NW + 2)),
-                     lds, stream, a);
+  const long blocks = (long)(SEG ? a.max_segs : a.N) * a.Hv;
+  hipLaunchKernelGGL((compact_walk_kernel<DK, DV, SINGLE, SEG>), dim3((unsigned)blocks), dim3(64 * (DV / 32 + 2)), lds,
+                     stream, a);
   return hipGetLastError();
 }
 
@@ -1014,9 +1000,8 @@ enum class Part { kWalk, kMaps, kSegments };
 
 template <int DK, int DV, bool SINGLE>
 hipError_t launch_dims(const PrefillArgs &a, Part part, hipStream_t s) {
-  constexpr int NW = DV / 32;
   if (part == Part::kMaps) return launch_map_t<DK, DV, SINGLE>(a, s);
-  if (part == Part::kSegments) return launch_walk_t<DK, DV, 2, NW, SINGLE, true>(a, s);
+  if (part == Part::kSegments) return launch_walk_t<DK, DV, SINGLE, true>(a, s);
   // The row walk while the column tiles, one or two to a workgroup, fit the CUs
   // in one round; beyond that a whole head per workgroup, which moves each
   // operand once for all its tiles.  Walk of 64 chunks, us, row walk against the
@@ -1025,7 +1010,7 @@ hipError_t launch_dims(const PrefillArgs &a, Part part, hipStream_t s) {
   const long tiles = ((long)a.N * a.Hv + kXcds - 1) / kXcds * kXcds * (DV / 16);
   if (tiles <= a.cus) return launch_row_t<DK, DV, 1, SINGLE>(a, s);
   if (tiles <= 2L * a.cus) return launch_row_t<DK, DV, 2, SINGLE>(a, s);
-  return launch_walk_t<DK, DV, 2, NW, SINGLE, false>(a, s);
+  return launch_walk_t<DK, DV, SINGLE, false>(a, s);
 }
 
 template <bool SINGLE>

@@ -695,13 +695,6 @@ hipError_t launch_maps_dims(const PrefillArgs &a, hipStream_t s) {
                   : launch_maps_t<bf16_t, DK, DV, false, TPW>(a, s);
 }
 
-hipError_t launch_maps_all(const PrefillArgs &a, hipStream_t s) {
-  if (a.Dk == 64 && a.Dv == 64) return launch_maps_dims<64, 64>(a, s);
-  if (a.Dk == 64 && a.Dv == 128) return launch_maps_dims<64, 128>(a, s);
-  if (a.Dk == 128 && a.Dv == 64) return launch_maps_dims<128, 64>(a, s);
-  return launch_maps_dims<128, 128>(a, s);
-}
-
 // The staged walk's LDS (three stages) exceeds the default 64 KiB limit: raise
 // it once per device and instance.
 template <typename T, int DK, int DV, bool SINGLE, int TPW>
@@ -741,17 +734,20 @@ hipError_t launch_walk_dims(const PrefillArgs &a, int cus, hipStream_t stream) {
   return launch_walk_single<bf16_t, DK, DV, 4>(a, groups, stream);
 }
 
-hipError_t launch_walk_all(const PrefillArgs &a, int cus, hipStream_t s) {
+}  // namespace
+
+hipError_t launch_seg_maps(const PrefillArgs &a, hipStream_t s) {
+  if (a.Dk == 64 && a.Dv == 64) return launch_maps_dims<64, 64>(a, s);
+  if (a.Dk == 64 && a.Dv == 128) return launch_maps_dims<64, 128>(a, s);
+  if (a.Dk == 128 && a.Dv == 64) return launch_maps_dims<128, 64>(a, s);
+  return launch_maps_dims<128, 128>(a, s);
+}
+
+hipError_t launch_state_walk(const PrefillArgs &a, int cus, hipStream_t s) {
   if (a.Dk == 64 && a.Dv == 64) return launch_walk_dims<64, 64>(a, cus, s);
   if (a.Dk == 64 && a.Dv == 128) return launch_walk_dims<64, 128>(a, cus, s);
   if (a.Dk == 128 && a.Dv == 64) return launch_walk_dims<128, 64>(a, cus, s);
   return launch_walk_dims<128, 128>(a, cus, s);
 }
-
-}  // namespace
-
-hipError_t launch_seg_maps(const PrefillArgs &a, hipStream_t s) { return launch_maps_all(a, s); }
-
-hipError_t launch_state_walk(const PrefillArgs &a, int cus, hipStream_t s) { return launch_walk_all(a, cus, s); }
 
 }  // namespace hagdn
