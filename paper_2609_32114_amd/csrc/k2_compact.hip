@@ -560,7 +560,7 @@ struct RowExchange {
   static constexpr int BYTES = off_d + TW * 2048;
 };
 
-template <int DK, int DV, int TW, bool SINGLE>
+template <int DK, int DV, int TW, bool SINGLE, bool SEG>
 __global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
   constexpr int NG = DV / (16 * TW), RT = DK / 16, KB = DK / 32, RPW = RT / 4;
   using X = RowExchange<DK, TW>;
@@ -570,10 +570,16 @@ __global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
   const int b = blockIdx.x;
   const int pair = (b / kXcds / NG) * kXcds + b % kXcds;  // the workgroups of a head share an XCD
   const int tg = (b / kXcds) % NG;
-  if (pair >= a.N * a.Hv) return;  // uniform for the workgroup
-  const int n = pair / a.Hv, h = pair % a.Hv;
+  if (pair >= (SEG ? a.max_segs : a.N) * a.Hv) return;  // uniform for the workgroup
+  const int s = pair / a.Hv, h = pair % a.Hv;            // sequence or segment, value head
+  int4 sg = {s, 0, 0, 0};  // {sequence, first chunk, chunks, index in sequence}
+  if constexpr (SEG) sg = seg_info_at<SINGLE>(a, s);
+  if (SEG && sg.x < 0) return;
+  const int n = sg.x;
   const int4 si = seq_info_at<SINGLE>(a, n);  // {first chunk, chunks, start, length}
-  const Span sp{si.x, si.y, si.z, si.w};
+  const int2 ss = SEG ? seq_seg_at<SINGLE>(a, n) : make_int2(0, 1);  // {first segment, segments}
+  const int skip = SEG ? sg.w * a.seg_chunks * kChunk : 0;           // tokens before the segment
+  const Span sp = SEG ? Span{sg.y, sg.z, si.z + skip, si.w - skip} : Span{si.x, si.y, si.z, si.w};
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int tile0 = tg * TW;
   if (w >= 4) {
@@ -583,13 +589,26 @@ __global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
   const int col = lane & 15, grp = lane >> 4;
   f32x4 H[TW][RPW];  // rows dk_of(w RPW + i, 4grp + e)
   const size_t sbase = ((size_t)n * a.Hv + h) * DK * DV;
+  if (SEG && sg.w > 0) {
+    // the state entering this segment (compact_scan_kernel)
+    const float *bm = a.Bseg + ((size_t)(s - 1) * a.Hv + h) * ((size_t)DK * DV);
 #pragma unroll
-  for (int t = 0; t < TW; ++t)
+    for (int t = 0; t < TW; ++t)
 #pragma unroll
-    for (int i = 0; i < RPW; ++i)
+      for (int i = 0; i < RPW; ++i)
+        H[t][i] = load4(bm + ((size_t)((tile0 + t) * RT + w * RPW + i) * 64 + lane) * 4);
+  } else {
+    // s0 itself only where one workgroup reads and writes its columns; else the
+    // copy the segment maps made (s_final may alias s0)
+    const float *src = SEG && ss.y > 1 && a.s0 ? a.s0c : a.s0;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        H[t][i][e] = a.s0 ? a.s0[sbase + (size_t)dk_of(w * RPW + i, 4 * grp + e) * DV + dv_of(tile0 + t, col)] : 0.f;
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          H[t][i][e] = src ? src[sbase + (size_t)dk_of(w * RPW + i, 4 * grp + e) * DV + dv_of(tile0 + t, col)] : 0.f;
+  }
 
   // LDS addresses, from a slot's base: key / query rows of token tile w, the
   // transposed keys of this wave's row tiles, the transposed values
@@ -617,7 +636,8 @@ __global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
 
   const size_t row_bytes = (size_t)a.Hv * DV * 2;
   const __amdgpu_buffer_rsrc_t orsrc =
-      rows_buffer(static_cast<unsigned char *>(a.o) + (size_t)sp.tok0 * row_bytes, (uint32_t)(sp.len * row_bytes));
+      rows_buffer(static_cast<unsigned char *>(a.o) + (size_t)sp.tok0 * row_bytes,
+                  (uint32_t)((SEG ? min(sp.len, sp.nch * kChunk) : sp.len) * row_bytes));
   int ooff = ((16 * w + col) * a.Hv + h) * DV * 2 + dv_of(tile0, 4 * grp) * 2;
   // ---- operands of chunk c, each read behind the barrier after its last use
   bf16x8 kf[KB], qf[KB], tf[2], pf[2], kt[RPW][2];
@@ -763,7 +783,7 @@ __global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
     }
     ooff += kChunk * (int)row_bytes;
   }
-  if (a.s_final) {
+  if (a.s_final && sg.w == ss.y - 1) {
 #pragma unroll
     for (int t = 0; t < TW; ++t)
 #pragma unroll
@@ -962,17 +982,18 @@ hipError_t launch_walk_t(const PrefillArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int DK, int DV, int TW, bool SINGLE>
+template <int DK, int DV, int TW, bool SINGLE, bool SEG>
 hipError_t launch_row_t(const PrefillArgs &a, hipStream_t stream) {
   using X = RowExchange<DK, TW>;
   constexpr int lds = Stage<DK, TW, true, X::BYTES>::BYTES + X::BYTES;
-  const void *kern = reinterpret_cast<const void *>(&compact_row_kernel<DK, DV, TW, SINGLE>);
+  const void *kern = reinterpret_cast<const void *>(&compact_row_kernel<DK, DV, TW, SINGLE, SEG>);
   static std::atomic<bool> done[kMaxDevices];
   hipError_t e = raise_lds(kern, lds, done);
   if (e != hipSuccess) return e;
-  const long groups = ((long)a.N * a.Hv + kXcds - 1) / kXcds;
+  const long groups = ((long)(SEG ? a.max_segs : a.N) * a.Hv + kXcds - 1) / kXcds;
   const long blocks = groups * kXcds * (DV / (16 * TW));
-  hipLaunchKernelGGL((compact_row_kernel<DK, DV, TW, SINGLE>), dim3((unsigned)blocks), dim3(64 * 6), lds, stream, a);
+  hipLaunchKernelGGL((compact_row_kernel<DK, DV, TW, SINGLE, SEG>), dim3((unsigned)blocks), dim3(64 * 6), lds, stream,
+                     a);
   return hipGetLastError();
 }
 
@@ -998,19 +1019,26 @@ hipError_t launch_map_t(const PrefillArgs &a, hipStream_t stream) {
 
 enum class Part { kWalk, kMaps, kSegments };
 
+// Whole chains, or segments with SEG.  The row walk while the column tiles, one
+// or two to a workgroup, fit the CUs in one round; beyond that a whole head per
+// workgroup, which moves each operand once for all its tiles.  Walk of 64 chunks,
+// us, row walk against the whole head: 32 heads 69 / 124 (one tile), 48 heads 90 /
+// 127 and 64 heads 104 / 129 (two tiles).  Segments of 1 x 7700 tokens, us per
+// call, the same way: d = 64, 1 head 42 / 48, 4 heads 47 / 52; d = 128, 1 head 57 /
+// 69 (the affine kernels took 42 and 50 at d = 64).
+template <int DK, int DV, bool SINGLE, bool SEG>
+hipError_t launch_walks(const PrefillArgs &a, hipStream_t s) {
+  const long tiles = ((long)(SEG ? a.max_segs : a.N) * a.Hv + kXcds - 1) / kXcds * kXcds * (DV / 16);
+  if (tiles <= a.cus) return launch_row_t<DK, DV, 1, SINGLE, SEG>(a, s);
+  if (tiles <= 2L * a.cus) return launch_row_t<DK, DV, 2, SINGLE, SEG>(a, s);
+  return launch_walk_t<DK, DV, SINGLE, SEG>(a, s);
+}
+
 template <int DK, int DV, bool SINGLE>
 hipError_t launch_dims(const PrefillArgs &a, Part part, hipStream_t s) {
   if (part == Part::kMaps) return launch_map_t<DK, DV, SINGLE>(a, s);
-  if (part == Part::kSegments) return launch_walk_t<DK, DV, SINGLE, true>(a, s);
-  // The row walk while the column tiles, one or two to a workgroup, fit the CUs
-  // in one round; beyond that a whole head per workgroup, which moves each
-  // operand once for all its tiles.  Walk of 64 chunks, us, row walk against the
-  // whole head: 32 heads 69 / 124 (one tile), 48 heads 90 / 127 and 64 heads 104
-  // / 129 (two tiles).
-  const long tiles = ((long)a.N * a.Hv + kXcds - 1) / kXcds * kXcds * (DV / 16);
-  if (tiles <= a.cus) return launch_row_t<DK, DV, 1, SINGLE>(a, s);
-  if (tiles <= 2L * a.cus) return launch_row_t<DK, DV, 2, SINGLE>(a, s);
-  return launch_walk_t<DK, DV, SINGLE, false>(a, s);
+  if (part == Part::kSegments) return launch_walks<DK, DV, SINGLE, true>(a, s);
+  return launch_walks<DK, DV, SINGLE, false>(a, s);
 }
 
 template <bool SINGLE>

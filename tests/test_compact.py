@@ -68,6 +68,35 @@ def test_segments_of_every_count(variant):
         P.set_segment_chunks(0)
 
 
+@pytest.mark.parametrize("lens", [(700,), (129, 0, 300)], ids=["one", "batch"])
+@pytest.mark.parametrize("heads", [1, 6, 12], ids=["tile", "pair", "head"])
+@pytest.mark.parametrize("dims", [(128, 128), (64, 64), (64, 128), (128, 64)], ids=lambda d: f"{d[0]}x{d[1]}")
+def test_segments_on_each_walk(dims, heads, lens):
+    """Segments of two chunks whose column tiles, one or two to a workgroup, fit 256
+    compute units (row walk) or do not (head walk), against the oracle and with
+    the final state written over the initial one."""
+    import torch
+    import paper_2609_32114_amd as P
+    Dk, Dv = dims
+    Hv, segs = heads * (128 // Dv), (sum(lens) // 64 + len(lens)) // 2 + len(lens)
+    tiles = -(-segs * Hv // 8) * 8 * (Dv // 16)
+    assert tiles <= 256 if heads == 1 else 256 < tiles <= 512 if heads == 6 else tiles > 512
+    inp = make_case("gdn", lens, Hv, Hv, Dk, Dv, "bf16", with_s0=True, variant="s0", seed=54, scale=Dk ** -0.5)
+    try:
+        P.set_segment_chunks(2)
+        check_against_oracle(inp, label="compact-segments")
+        d = to_device(inp)
+        run = lambda s0, out: P.gdn_prefill(d["q"], d["k"], d["v"], d["g"], d["beta"], initial_state=s0,  # noqa: E731
+                                            cu_seqlens=d["cu"], scale=inp.scale, final_out=out)
+        o1, s1 = run(d["s0"], None)
+        state = d["s0"].clone()
+        o2, _ = run(state, state)
+        torch.cuda.synchronize()
+    finally:
+        P.set_segment_chunks(0)
+    assert torch.equal(o1, o2) and torch.equal(state, s1)
+
+
 def test_workspace_regions_of_a_compact_call():
     import paper_2609_32114_amd as P
     for T, Hv, held in ((200, 2, True), (32768, 16, False), (4096, 64, False)):
