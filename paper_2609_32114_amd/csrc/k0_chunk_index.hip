@@ -144,6 +144,20 @@ __global__ __launch_bounds__(kIndexThreads) void chunk_index_kernel(PrefillArgs 
     }
     a.seg_info[sg] = info;
   }
+  if (a.long_rows > 0) {  // the long sequences, in any order
+    __shared__ int s_long;
+    if (tid == 0) s_long = 0;
+    __syncthreads();  // also: the searches above are done with seq_info
+    for (int n = tid; n < N; n += kIndexThreads) {
+      const int4 s = lds_tables ? s_info[n] : a.seq_info[n];
+      if (is_long_chain(a, s.y, total)) {
+        a.ovl[1 + atomicAdd(&s_long, 1)] = n;
+        a.seq_info[n].x = s.x | kLongMark;
+      }
+    }
+    __syncthreads();
+    if (tid == 0) a.ovl[0] = s_long;
+  }
   if (tid == 0) a.status[0] = bad ? 1 : 0;
 }
 

@@ -475,11 +475,9 @@ __device__ __forceinline__ void store_chunk(__amdgpu_buffer_rsrc_t rsrc, int off
 // adjacent 16-column tiles each) and two loader waves per (sequence, value
 // head), or with SEG per (segment, value head).
 template <int DK, int DV, bool SINGLE, bool SEG>
-__global__ __launch_bounds__(64 * (DV / 32 + 2), 1) void compact_walk_kernel(PrefillArgs a) {
+__device__ __forceinline__ void head_walk(const PrefillArgs &a, int pair) {
   constexpr int TW = 2, NW = DV / 32, CT = DV / 16, RT = DK / 16;
   extern __shared__ __align__(16) unsigned char lds[];
-  single_status<SINGLE>(a);
-  const int pair = blockIdx.x;
   const int s = pair / a.Hv, h = pair % a.Hv;           // sequence or segment, value head
   int4 sg = {s, 0, 0, 0};  // {sequence, first chunk, chunks, index in sequence}
   if constexpr (SEG) sg = seg_info_at<SINGLE>(a, s);
@@ -542,6 +540,12 @@ __global__ __launch_bounds__(64 * (DV / 32 + 2), 1) void compact_walk_kernel(Pre
   }
 }
 
+template <int DK, int DV, bool SINGLE, bool SEG>
+__global__ __launch_bounds__(64 * (DV / 32 + 2), 1) void compact_walk_kernel(PrefillArgs a) {
+  single_status<SINGLE>(a);
+  head_walk<DK, DV, SINGLE, SEG>(a, blockIdx.x);
+}
+
 // ---------------------------------------------------------------------------
 // Row walk: the latency form of the state walk, for calls whose column tiles do
 // not outnumber the CUs much.  Four waves share TW tiles: wave w owns token tile
@@ -560,23 +564,20 @@ struct RowExchange {
   static constexpr int BYTES = off_d + TW * 2048;
 };
 
-template <int DK, int DV, int TW, bool SINGLE, bool SEG>
-__global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
-  constexpr int NG = DV / (16 * TW), RT = DK / 16, KB = DK / 32, RPW = RT / 4;
+// Column tiles tg TW .. of chain `pair`; LONG: its sequence is marked as long.
+template <int DK, int DV, int TW, bool SINGLE, bool SEG, bool LONG = false>
+__device__ __forceinline__ void row_walk(const PrefillArgs &a, int pair, int tg) {
+  constexpr int RT = DK / 16, KB = DK / 32, RPW = RT / 4;
   using X = RowExchange<DK, TW>;
   using S = Stage<DK, TW, true, X::BYTES>;
   extern __shared__ __align__(16) unsigned char lds[];
-  single_status<SINGLE>(a);
-  const int b = blockIdx.x;
-  const int pair = (b / kXcds / NG) * kXcds + b % kXcds;  // the workgroups of a head share an XCD
-  const int tg = (b / kXcds) % NG;
-  if (pair >= (SEG ? a.max_segs : a.N) * a.Hv) return;  // uniform for the workgroup
   const int s = pair / a.Hv, h = pair % a.Hv;            // sequence or segment, value head
   int4 sg = {s, 0, 0, 0};  // {sequence, first chunk, chunks, index in sequence}
   if constexpr (SEG) sg = seg_info_at<SINGLE>(a, s);
   if (SEG && sg.x < 0) return;
   const int n = sg.x;
-  const int4 si = seq_info_at<SINGLE>(a, n);  // {first chunk, chunks, start, length}
+  int4 si = seq_info_at<SINGLE>(a, n);  // {first chunk, chunks, start, length}
+  if constexpr (LONG) si.x &= ~kLongMark;
   const int2 ss = SEG ? seq_seg_at<SINGLE>(a, n) : make_int2(0, 1);  // {first segment, segments}
   const int skip = SEG ? sg.w * a.seg_chunks * kChunk : 0;           // tokens before the segment
   const Span sp = SEG ? Span{sg.y, sg.z, si.z + skip, si.w - skip} : Span{si.x, si.y, si.z, si.w};
@@ -759,7 +760,14 @@ __global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) uf[t][kb] = lds_frag(xu + (2 * t + kb) * 1024);
     __builtin_amdgcn_sched_barrier(0);
-    read_keys(c + 1);
+    // the next chunk's operands: at d_k = 64 the keys before the update's products
+    // and the queries before the outputs', at 128 all behind them (the products of a
+    // step then wait for fewer reads; 64 chunks with 20 heads, either order left to
+    // the compiler: 65-77 us against 62-73 at 64, 81 against 77 at 128)
+    if constexpr (DK == 64) {
+      read_keys(c + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -768,11 +776,19 @@ __global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
         for (int i = 0; i < RPW; ++i) H[t][i] = mma(H[t][i], kt[i][kb], df[t][kb]);
     put_state();
     __builtin_amdgcn_sched_barrier(0);
-    read_queries(c + 1);
+    if constexpr (DK == 64) {
+      read_queries(c + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int t = 0; t < TW; ++t) {
       o[t] = mma(o[t], uf[t][0], pf[0]);
       o[t] = mma(o[t], uf[t][1], pf[1]);
+    }
+    if constexpr (DK != 64) {
+      read_keys(c + 1);
+      read_queries(c + 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (TW == 2) {
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, frag_from_acc<bf16_t>(o[0], o[1])), orsrc, ooff, 0,
@@ -791,6 +807,56 @@ __global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           a.s_final[sbase + (size_t)dk_of(w * RPW + i, 4 * grp + e) * DV + dv_of(tile0 + t, col)] = H[t][i][e];
+  }
+}
+
+// Workgroup b of a launch of NG workgroups per chain: the chain and its part.  The
+// workgroups of a head share an XCD.
+template <int NG>
+__device__ __forceinline__ int chain_of(int b) {
+  return (b / kXcds / NG) * kXcds + b % kXcds;
+}
+template <int NG>
+__device__ __forceinline__ int part_of(int b) {
+  return (b / kXcds) % NG;
+}
+
+template <int DK, int DV, int TW, bool SINGLE, bool SEG>
+__global__ __launch_bounds__(64 * 6, 1) void compact_row_kernel(PrefillArgs a) {
+  constexpr int NG = DV / (16 * TW);
+  single_status<SINGLE>(a);
+  const int b = blockIdx.x, pair = chain_of<NG>(b);
+  if (pair >= (SEG ? a.max_segs : a.N) * a.Hv) return;  // uniform for the workgroup
+  row_walk<DK, DV, TW, SINGLE, SEG>(a, pair, part_of<NG>(b));
+}
+
+// Whole chains of a batch that has more column tiles than CUs and may hold chains much
+// longer than the others (prefill.h, is_long_chain): the long ones' tiles first, one to
+// a workgroup (row walk), then the other chains as a launch without them would walk
+// them, in tile pairs (PAIR) or whole heads.  The chunk index kernel left the long
+// sequences in a.ovl and a mark in their entries, so a workgroup reads nothing more
+// than the plain walk does (with the count read first by every workgroup, 201 short
+// sequences of 32 heads took 7 % longer).  Walked like the others, one 4,096-token
+// chain among empty ones took 78 (pairs) or 122 us at d = 128 and 58 or 84 at 64, for
+// the row walk's 60 and 50; calls with such a chain were up to 1.48 times as long as
+// with the affine factors.
+template <int DK, int DV, bool PAIR>
+__global__ __launch_bounds__(64 * 6, 1) void compact_mixed_kernel(PrefillArgs a) {
+  constexpr int NT = DV / 16, NG = PAIR ? NT / 2 : 1;
+  const int b = blockIdx.x;
+  if (b < a.long_rows) {
+    const int i = chain_of<NT>(b);
+    if (i >= a.ovl[0] * a.Hv) return;  // uniform for the workgroup, as every return here
+    row_walk<DK, DV, 1, false, false, true>(a, a.ovl[1 + i / a.Hv] * a.Hv + i % a.Hv, part_of<NT>(b));
+    return;
+  }
+  const int pair = chain_of<NG>(b - a.long_rows);
+  if (pair >= a.N * a.Hv || a.seq_info[pair / a.Hv].x < 0) return;
+  if constexpr (PAIR) {
+    row_walk<DK, DV, 2, false, false>(a, pair, part_of<NG>(b - a.long_rows));
+  } else {
+    if (threadIdx.x >= 64 * (DV / 32 + 2)) return;  // whole waves (ended waves do not count at a barrier)
+    head_walk<DK, DV, false, false>(a, pair);
   }
 }
 
@@ -997,6 +1063,22 @@ hipError_t launch_row_t(const PrefillArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <int DK, int DV, bool PAIR>
+hipError_t launch_mixed_t(const PrefillArgs &a, hipStream_t stream) {
+  using X1 = RowExchange<DK, 1>;
+  using X2 = RowExchange<DK, 2>;
+  constexpr int lds1 = Stage<DK, 1, true, X1::BYTES>::BYTES + X1::BYTES;
+  constexpr int lds2 = PAIR ? Stage<DK, 2, true, X2::BYTES>::BYTES + X2::BYTES : Stage<DK, DV / 16, true>::BYTES;
+  constexpr int lds = lds1 > lds2 ? lds1 : lds2, NT = DV / 16;
+  const void *kern = reinterpret_cast<const void *>(&compact_mixed_kernel<DK, DV, PAIR>);
+  static std::atomic<bool> done[kMaxDevices];
+  hipError_t e = raise_lds(kern, lds, done);
+  if (e != hipSuccess) return e;
+  const long rest = ((long)a.N * a.Hv + kXcds - 1) / kXcds * kXcds * (PAIR ? NT / 2 : 1);
+  hipLaunchKernelGGL((compact_mixed_kernel<DK, DV, PAIR>), dim3((unsigned)(a.long_rows + rest)), dim3(64 * 6), lds, stream, a);
+  return hipGetLastError();
+}
+
 template <int DK, int DV, bool SINGLE>
 hipError_t launch_map_t(const PrefillArgs &a, hipStream_t stream) {
   constexpr int rings = Stage<DK, DV / 16, false>::BYTES, tr = DK * (DK + 8) * 2;
@@ -1030,6 +1112,10 @@ template <int DK, int DV, bool SINGLE, bool SEG>
 hipError_t launch_walks(const PrefillArgs &a, hipStream_t s) {
   const long tiles = ((long)(SEG ? a.max_segs : a.N) * a.Hv + kXcds - 1) / kXcds * kXcds * (DV / 16);
   if (tiles <= a.cus) return launch_row_t<DK, DV, 1, SINGLE, SEG>(a, s);
+  if constexpr (!SINGLE && !SEG) {
+    if (a.long_rows > 0)
+      return tiles <= 2L * a.cus ? launch_mixed_t<DK, DV, true>(a, s) : launch_mixed_t<DK, DV, false>(a, s);
+  }
   if (tiles <= 2L * a.cus) return launch_row_t<DK, DV, 2, SINGLE, SEG>(a, s);
   return launch_walk_t<DK, DV, SINGLE, SEG>(a, s);
 }

@@ -94,7 +94,22 @@ struct PrefillArgs {
   // block at kOvlFlags + blk.  All zero before the launch (overlap_setup).
   int *ovl;
   int ovl_walk_wgs;
+  // Compact whole-chain walks that treat long chains apart: the workgroups for
+  // their column tiles, else 0 (long_chain_rows).  The chunk index kernel then
+  // leaves {long sequences, their numbers ..} in ovl and marks their entries of
+  // seq_info (kLongMark in the first chunk).
+  int long_rows;
 };
+
+constexpr int kLongMark = (int)0x80000000;
+// Whether a chain of nch chunks is long beside the batch's `total`: its column
+// tiles, one to a CU, and those of every chain as long fit the CUs together (so
+// fewer than cus / (Hv Dv / 16) sequences are long).  The others' work, even spread
+// over the CUs that are left, then ends before the long chains do: per head and
+// chunk a whole head's step takes a CU 4 us at most, a column tile of the row walk 1.
+__host__ __device__ inline bool is_long_chain(const PrefillArgs &a, int nch, int total) {
+  return (long)nch * a.cus > (long)a.Hv * (a.Dv / 16) * total;
+}
 
 // XCDs of an MI355X.  Each has its own L2; the L2s are not coherent with each
 // other within a kernel.

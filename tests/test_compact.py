@@ -97,6 +97,39 @@ def test_segments_on_each_walk(dims, heads, lens):
     assert torch.equal(o1, o2) and torch.equal(state, s1)
 
 
+LONG = [  # lengths, value heads at d_v = 128 (twice as many at 64)
+    ((20,) * 7 + (3000,) + (20,) * 8, 4),               # tile pairs beside one long sequence
+    ((20,) * 30 + (2000, 0, 1500, 65), 4),              # whole heads beside two
+    ((2,) * 299 + (2500,), 1),                          # more sequences than the index kernel's threads
+]
+
+
+@pytest.mark.parametrize("case", LONG, ids=["pairs", "heads", "many"])
+@pytest.mark.parametrize("dims", [(128, 128), (64, 64), (64, 128), (128, 64)], ids=lambda d: f"{d[0]}x{d[1]}")
+def test_long_sequences_among_short_ones(dims, case):
+    """Batches with more column tiles than 256 compute units in which some
+    sequences are so much longer than the others that they are walked apart,
+    against the oracle and with the final state written over the initial one."""
+    import torch
+    import paper_2609_32114_amd as P
+    Dk, Dv = dims
+    lens, Hv = case[0], case[1] * (128 // Dv)
+    chunks = [-(-n // 64) for n in lens]
+    share, tiles = Hv * Dv // 16, -(-len(lens) * Hv // 8) * 8 * (Dv // 16)
+    assert tiles > 256 and sum(lens) >= 64 * (48 if tiles <= 512 else 32) - 63
+    assert (tiles <= 512) == (len(lens) == 16) and max(chunks) * 256 > share * sum(chunks)
+    inp = make_case("gdn", lens, Hv, Hv, Dk, Dv, "bf16", with_s0=True, variant="s0", seed=55, scale=Dk ** -0.5)
+    check_against_oracle(inp, label="compact-long")
+    d = to_device(inp)
+    run = lambda s0, out: P.gdn_prefill(d["q"], d["k"], d["v"], d["g"], d["beta"], initial_state=s0,  # noqa: E731
+                                        cu_seqlens=d["cu"], scale=inp.scale, final_out=out)
+    o1, s1 = run(d["s0"], None)
+    state = d["s0"].clone()
+    o2, _ = run(state, state)
+    torch.cuda.synchronize()
+    assert torch.equal(o1, o2) and torch.equal(state, s1)
+
+
 def test_workspace_regions_of_a_compact_call():
     import paper_2609_32114_amd as P
     for T, Hv, held in ((200, 2, True), (32768, 16, False), (4096, 64, False)):
