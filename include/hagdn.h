@@ -339,9 +339,9 @@ int hagdn_measure_mfma(int iterations, float *sink, size_t sink_floats, double *
  * B and O_loc lane-major per 16-column state tile with the tile's columns
  * interleaved in pairs of tiles (csrc/prefill.h gives the exact maps).
  * GDN calls in bf16 whose chains are cut into segments or whose walks (N x Hv x
- * Dv/16) outnumber half the compute units keep a more compact form of the factors
- * in the same place (csrc/compact.h): for them *bytes is 0 for NM .. DECAY, and
- * the segment maps use the compact walk's own row order.
+ * Dv/16) outnumber half the compute units (a long batch: all of them) keep a more
+ * compact form of the factors in the same place (csrc/compact.h): for them *bytes
+ * is 0 for NM .. DECAY, and the segment maps use the compact walk's own row order.
  * Returns HAGDN_OK or HAGDN_EINVAL.  Depends on the device like the
  * workspace size. */
 typedef enum {

@@ -238,13 +238,28 @@ bool overlap_applies(bool bf16, bool kda, int Dk, int Dv, bool maps, int N, int 
 // CUs: 1 x 4096 tokens with 20 heads 119 / 86, 32 heads 152 / 95, 64 heads 284 /
 // 150; 4 x 500 tokens, 16 heads 46 / 31; 8 sequences, 34,800 tokens, 32 heads
 // 1124 / 511; 20 sequences, 6,100 tokens, 32 heads, raw projections 268 / 115;
-// 1 x 32768 tokens, 16 heads (segments) 686 / 326.  Up to half the CUs the
-// affine walk's shorter step decides, and its overlapped launch.
-bool compact_applies(bool bf16, bool kda, bool maps, int N, int Hv, int Dv, int cus) {
+// 1 x 32768 tokens, 16 heads (segments) 686 / 326.
+// Up to half the CUs the affine factors stay, with the overlapped launch; where
+// that line should lie for them was not measured.
+// Up to one walk per CU the affine walk has the shorter step, by 0.18 us at d_k =
+// 128 and 0.27 at 64, and one sequence of a batch may be nearly as long as the batch,
+// which the host cannot see.  There the compact form is taken where even such a
+// chain would end no later: its chunk-local kernel saves 10 us (5.5 at d_k = 64) and,
+// per block, of which there is one per head and chunk at least, 9 to 28 ns.  us,
+// affine against compact: 8,000 tokens beside 31 sequences of 20, 2 heads, d = 64
+// 73 / 100; what the bound gives up where the lengths are even: 32 x 500 tokens, 2
+// heads, d = 64 30 / 24, 16 x 1,000 tokens, 2 heads, d = 128 46 / 34.  Choosing on the
+// device instead cost 4 us for the chunk-local launch that finds nothing to do, and
+// the affine walk 10 % in a kernel with the other.
+bool compact_applies(bool bf16, bool kda, bool maps, int N, int T, int Hv, int Dk, int Dv, int cus) {
   if (!bf16 || kda) return false;
   if (maps) return true;
   const long walks = ((long)N * Hv + hagdn::kXcdCount - 1) / hagdn::kXcdCount * hagdn::kXcdCount * (Dv / 16);
-  return walks > cus / 2;
+  if (walks <= cus / 2) return false;
+  if (walks > cus || N == 1) return true;
+  const double chunks = (double)chunks_of(T);
+  const double block_us = (Dk == 64 ? (Dv == 64 ? 9.4 : 13.5) : (Dv == 64 ? 19.0 : 28.5)) * 1e-3;
+  return chunks * (Dk == 64 ? 0.27 : 0.18) <= (Dk == 64 ? 5.5 : 10.0) + chunks * Hv * block_us;
 }
 
 // Workgroups for the column tiles of long chains (is_long_chain) in a compact call
@@ -345,7 +360,7 @@ int prefill(bool kda, const void *q, const void *k, const void *v, const float *
   a.ovl_walk_wgs = 0;
   const bool maps = chunks_of(T) > L.seg_chunks;
   const bool overlap = T > 0 && overlap_applies(bf16, kda, Dk, Dv, maps, N, T, Hv, cus);
-  const bool compact = compact_applies(bf16, kda, maps, N, Hv, Dv, cus);
+  const bool compact = compact_applies(bf16, kda, maps, N, T, Hv, Dk, Dv, cus);
   a.long_rows = compact && !maps && !overlap ? long_chain_rows(N, T, Hv, Dv, cus) : 0;
 
   hipStream_t st = static_cast<hipStream_t>(stream_);
@@ -681,7 +696,7 @@ int hagdn_workspace_region(int kda, int N, int T_total, int Hqk, int Hv, int Dk,
   const bool bf16 = dtype == HAGDN_BF16;
   const bool maps = chunks_of(T_total) > L.seg_chunks;
   // a compact call keeps none of the affine factors
-  const bool compact = compact_applies(bf16, kda != 0, maps, N, Hv, Dv, query_cus());
+  const bool compact = compact_applies(bf16, kda != 0, maps, N, T_total, Hv, Dk, Dv, query_cus());
   size_t at, next;
   switch (region) {
     case HAGDN_WS_NM: at = L.NM; next = L.Bc; break;

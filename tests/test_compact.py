@@ -137,6 +137,20 @@ def test_workspace_regions_of_a_compact_call():
             assert (P.workspace_region("gdn", 1, T, Hv, Hv, 128, 128, P.HAGDN_BF16, r)[1] > 0) == held
 
 
+@pytest.mark.parametrize("dims,lens,heads", [((64, 64), (40,) * 7 + (4000,), 8), ((128, 128), (40,) * 15 + (5500,), 2)],
+                         ids=["64x64", "128x128"])
+def test_batch_that_may_hold_one_long_sequence_keeps_the_affine_factors(dims, lens, heads):
+    """129 to 256 column tiles: a long batch keeps the affine factors, whose walk has
+    the shorter step; a short one takes the compact form."""
+    import paper_2609_32114_amd as P
+    Dk, Dv = dims
+    assert 128 < len(lens) * heads * Dv // 16 <= 256
+    nm = lambda T: P.workspace_region("gdn", len(lens), T, heads, heads, Dk, Dv, P.HAGDN_BF16, P.WS_NM)[1]  # noqa: E731
+    assert nm(1000) == 0 and nm(sum(lens)) > 0
+    inp = make_case("gdn", lens, heads, heads, Dk, Dv, "bf16", with_s0=True, variant="s0", seed=56, scale=Dk ** -0.5)
+    check_against_oracle(inp, label="affine-batch")
+
+
 def test_in_place_state_batch():
     import torch
     import paper_2609_32114_amd as P
