@@ -4,9 +4,11 @@ Every output (o, s_final, the decode state pool and output) and the workspace
 sit inside a larger allocation whose guard zones before and after are filled
 with a byte pattern; after the call the guards must be intact.  The cases
 reach every launch path: the overlapped launch, the serialized four-wave walk,
-the staged walk (more walks than CUs), the segment maps and segment walks
-(bf16 and fp32 maps), fp32 with d = 64, the allocation-free entry point and
-decode over a slot-addressed pool.
+the compact walks (GDN in bf16: one tile, tile pairs, whole heads, long sequences
+walked apart) and their segment maps, scan and segment walks, KDA's staged walk
+(more walks than CUs), the segment maps and segment walks (bf16 and fp32 maps),
+fp32 with d = 64, the allocation-free entry point and decode over a slot-addressed
+pool.
 """
 
 import numpy as np
@@ -39,7 +41,17 @@ CASES = [
     # kind, lengths, Hqk, Hv, D, dtype, segment chunks (0: automatic), overlap forced where it can run
     ("gdn", (1000,), 4, 16, 128, "bf16", 0, True),          # overlapped launch
     ("gdn", (1000,), 4, 16, 128, "bf16", 0, False),         # serialized four-wave walk (too short to overlap)
-    ("gdn", (300, 0, 1, 777), 12, 12, 128, "bf16", 0, True),  # staged walk: 384 walks
+    ("gdn", (300, 0, 1, 777), 12, 12, 128, "bf16", 0, True),  # compact row walk in tile pairs: 384 walks
+    ("gdn", (333,), 10, 20, 128, "bf16", 0, True),          # compact row walk, one tile: 160 walks of one sequence
+    ("gdn", (300, 0, 1, 777), 12, 24, 64, "bf16", 0, True),  # pairs, d = 64
+    ("gdn", (300, 0, 1, 777, 65), 4, 16, 128, "bf16", 0, True),  # compact head walk: 640 walks
+    ("gdn", (90, 60, 129), 4, 80, 64, "bf16", 0, True),     # head walk, d = 64
+    ("gdn", (20,) * 7 + (3000,) + (20,) * 8, 4, 4, 128, "bf16", 0, True),  # pairs beside one long sequence
+    ("gdn", (700, 65), 2, 4, 128, "bf16", 2, True),         # compact maps, scan, segments on the row walk
+    ("gdn", (700, 129), 8, 24, 128, "bf16", 2, True),       # the same on the head walk
+    ("gdn", (700, 129), 8, 24, 64, "bf16", 2, True),
+    ("kda", (300, 0, 1, 777), 12, 12, 128, "bf16", 0, True),  # staged walk, two tiles: 384 walks
+    ("kda", (130, 70, 0, 65), 8, 40, 64, "bf16", 0, True),  # staged walk, four tiles
     ("kda", (1000,), 2, 8, 128, "bf16", 3, True),           # bf16 segment maps + segment walks
     ("gdn", (700, 65), 2, 6, 64, "f32", 4, True),           # fp32 maps, d = 64
     ("kda", (129,), 1, 3, 64, "f32", 0, True),
