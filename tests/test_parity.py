@@ -256,7 +256,9 @@ def test_bad_seqlens_single_sequence(kind):
 
 @pytest.mark.parametrize("case", [
     ("gdn", (1000, 333), 2, 4),          # four-wave walk
-    ("gdn", (300, 200, 150), 8, 16),     # staged walk, two tiles per workgroup
+    ("gdn", (300, 200, 150), 8, 16),     # compact row walk, two tiles per workgroup
+    ("gdn", (130, 70, 200, 65), 8, 40),  # compact head walk
+    ("kda", (300, 200, 150), 8, 16),     # staged walk, two tiles per workgroup
     ("kda", (130, 70, 200, 65), 8, 40),  # staged walk, four tiles per workgroup
 ], ids=lambda c: f"{c[0]}-N{len(c[1])}-Hv{c[3]}")
 def test_bitwise_deterministic(case):
@@ -299,14 +301,15 @@ def test_workload2_shape_stress(variant):
 
 @pytest.mark.parametrize("variant", ["lm", "dn", "ks"])
 def test_workload4_shape_stress(variant):
-    """Workload 4's shape (2048 walks: the staged walk, four tiles per
-    workgroup) with gates that carry the state across every chunk."""
+    """Workload 4's shape (2048 walks: the compact head walk) with gates that
+    carry the state across every chunk."""
     inp = make_workload(4, variant=variant)
     check_against_oracle(inp, label=f"workload4-{variant}")
 
 
-# More walk workgroups than CUs (N x Hv x Dv/16 > 256): bf16 chains take the
-# staged walk, two or four column tiles per workgroup.
+# More walks than CUs (N x Hv x Dv/16 > 256): KDA in bf16 takes the staged walk,
+# two or four column tiles per workgroup, GDN the compact walks, tile pairs or (past
+# 512 walks) whole heads.
 # Long-memory gates so that the state carries across every chunk; the oracle
 # checks every head.
 MANY_WALKS = [

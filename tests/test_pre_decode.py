@@ -77,14 +77,16 @@ def test_prefill_preprocessing_matches_oracle(case):
     _check("s_final", sf, rs, TOL[dtype])
 
 
-# the flagged chunk-local instance feeding the other chain kernels: the bf16
-# segment maps (forced short segments) and the staged walk (more walks than
-# compute units: 3 sequences x 12 heads x 8 column tiles = 320 walks)
+# the flagged chunk-local instances feeding the other chain kernels: KDA's bf16
+# segment maps and the compact ones (forced short segments), the compact row walk
+# in tile pairs and the staged walk (more walks than compute units: 3 sequences x
+# 12 heads x 8 column tiles = 288 walks, 320 with the heads padded to whole XCDs)
 PRE_CHAIN_CASES = [
     # kind, lengths, Hqk, Hv, segment chunks (0: automatic)
     ("kda", (700,), 2, 4, 3),
     ("gdn", (400, 130), 2, 4, 2),
     ("gdn", (130, 257, 64), 4, 12, 0),
+    ("kda", (130, 257, 64), 4, 12, 0),
 ]
 
 
