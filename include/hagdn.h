@@ -100,7 +100,9 @@ typedef enum {
  * holds the chunk and segment tables and the chunk-local factors of operators
  * #2-#6 (the state-independent parts of the per-chunk state update and output,
  * after Sec. 5's GEMM-first regrouping): Dk*Dk + Dk*Dv + 64*(Dk+Dv) elements
- * plus Dk floats per (chunk, value head) for chunks bounded by T/64 + N.  When
+ * plus Dk floats per (chunk, value head) for chunks bounded by T/64 + N.  A GDN
+ * call in bf16 that keeps the compact factors (hagdn_workspace_region) uses 13 KiB
+ * of each such block; the size is the same.  When
  * a sequence can span more than one segment of the state chain (Sec. 4's
  * Chunk-Seg-Seg mapping; see hagdn_segment_chunks) it also holds one segment
  * map, Dk*Dk elements plus Dk*Dv floats, per (segment, value head) for

@@ -90,7 +90,11 @@ int query_cus() {
 // operands through one CU), on about (n / L) Hv workgroups.
 //
 // The thresholds come from sweeps of single sequences on an MI355X (256 CUs;
-// d = 128, bf16, operator totals in us, whole chain against the best L):
+// d = 128, bf16, operator totals in us, whole chain against the best L), all with
+// the affine factors' kernels.  KDA and fp32 run these; GDN in bf16 segments, and
+// walks whole beyond half the CUs, with the compact kernels since (compact.h: maps
+// of 2.8 us a step, a scan instead of the prefix, walks of 1 to 4 us), for which
+// neither the threshold nor L was swept again:
 //   GDN, 16 heads (128 walk workgroups, half the CUs): T = 6144 (96 chunks)
 //     135 against 141 (L = 12); 7168 (112) 162 against 161 (L = 8); 8192
 //     (128) 185 against 176 (L = 12); 9216 235 against 200; 12288 341

@@ -60,8 +60,7 @@ __device__ __forceinline__ void wait_loads() {
 // value, so an operand read (one piece of 16 rows) meets no bank twice; its
 // upper bits follow r's lowest ones, so the four rows of a transposed read's
 // 16-lane group (four pieces each) cover all pieces of a row.  With the plain
-// r mod 16 those four rows met in the same four pieces, and the LDS spent 960 of
-// 2150 active cycles per chunk step on conflicts.
+// r mod 16 those four rows meet in the same four pieces.
 template <int ROW>
 __device__ __forceinline__ constexpr int row_swz(int r) {
   return ROW >= 256 ? ((r & 3) << 2) | ((r >> 2) & 3) : ROW == 128 ? ((r & 1) << 2) | ((r >> 1) & 3) : r & (ROW / 16 - 1);

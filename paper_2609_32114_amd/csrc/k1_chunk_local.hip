@@ -97,10 +97,10 @@ struct LocalLayout {
 // KDA gamma[r][d] in the [64][DK] table, rows unpadded: the 16-byte chunk q of
 // row r is stored at chunk q ^ f(r), f(r) = (r & 7) ^ 4 ((r >> 3) & 1).  The
 // (r & 7) term lets eight consecutive token rows read the same channels as
-// 16-byte vectors with no bank conflict (op #2, Q'); the second term puts
-// token rows 8 apart into different halves of a 32-channel block, so the
-// per-element reads of op #4 (16 channels x 4 token rows 8 apart) conflict at
-// most 2-way.  Chunks move only inside their 32-channel block.
+// 16-byte vectors with no bank conflict (op #2, Q', and the key rows that are
+// staged with one token per lane).  The second term puts token rows 8 apart into
+// different halves of a 32-channel block, for per-element reads of four such rows;
+// no read needs it any more.  Chunks move only inside their 32-channel block.
 template <int DK>
 __device__ __forceinline__ int gam_at(int r, int d) {
   const int f = (r & 7) ^ (((r >> 3) & 1) << 2);

@@ -14,10 +14,11 @@
 // It then inverts its diagonal block and solves column block i of T
 // (chunk_item.h), whose transposed blocks are halves of T' operand blocks.
 // Four barriers in all (keys staged, and free again, A and the T_ii published,
-// and with raw keys their L2 factors).  A takes the keys' place in LDS, so five
-// workgroups share a CU (17.5 KiB of LDS, under 96 registers); in a place of its
-// own, at four per CU and one barrier less, the last three calls below took 162-183,
-// 44 and 90.  us, affine kernel against this one: one block per CU 19.7 / 8; 1,024
+// and with raw keys their L2 factors).  Five workgroups share a CU, as many as the
+// registers allow (under 96).  A takes the keys' place in LDS: 17 KiB a workgroup;
+// with a place of its own, 33 KiB, at four per CU and one barrier less, the last
+// three calls below took 162-183, 44 and 90.  us, affine kernel against this one: one
+// block per CU 19.7 / 8; 1,024
 // blocks 47.5 / 15.6; 17,408 with two heads per key head 604-669 / 148-167; 3,200
 // raw ones 134-145 / 42; 8,192 with 1 x 32768 tokens 293-326 / 76-87 (411 MB, the
 // rate of a large copy).  Six per CU spill.
@@ -35,7 +36,7 @@ __global__ __launch_bounds__(kThreads, 5) void chunk_compact_kernel(PrefillArgs 
   constexpr int RPB = 1024 / ROW;       // rows of one 1 KiB load
   constexpr int LPW = kChunk / RPB / 4; // loads per wave
   // keys until op #2 is done with them, then A (strictly lower blocks) and T_ii
-  // (diagonal blocks): 17.5 KiB a workgroup, so five share a CU
+  // (diagonal blocks): 17 KiB a workgroup with the token vectors
   constexpr int kTile = kChunk * ROW > kChunk * kChunk * 4 ? kChunk * ROW : kChunk * kChunk * 4;
   __shared__ __align__(16) unsigned char sK[kTile];
   float *sA = reinterpret_cast<float *>(sK);

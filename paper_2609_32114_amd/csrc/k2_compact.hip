@@ -553,10 +553,11 @@ __global__ __launch_bounds__(64 * (DV / 32 + 2), 1) void compact_walk_kernel(Pre
 // dependent products of a step are a few MFMAs each, and S, X and U pass
 // between the waves as operand fragments through LDS (three barriers a step).
 // A step takes ~2,000 cycles (62 us for 64 chunks), against ~3,200 for one wave
-// per tile: the LDS moves ~160 KiB in it at about 128 bytes a clock (operands in
-// and out, exchange).  Q, T' and P' straight to their one reader's registers (two
-// chunks ahead, or one behind a loader that touched their lines) took 74 and
-// 78 us: the waits for those loads cost more than the LDS bytes they save.
+// per tile: at d_k = 128 and one tile the LDS moves ~165 KiB in it (49 staged, 66
+// read as operands, 50 exchanged), 1,300 cycles at 128 bytes a clock.  Q, T' and P'
+// straight to their one reader's registers (two chunks ahead, or one behind a loader
+// that touched their lines) took 74 and 78 us: the waits for those loads cost more
+// than the LDS bytes they save.
 template <int DK, int TW>
 struct RowExchange {
   static constexpr int KB = DK / 32;
