@@ -107,8 +107,13 @@ constexpr int kLongMark = (int)0x80000000;
 // fewer than cus / (Hv Dv / 16) sequences are long).  The others' work, even spread
 // over the CUs that are left, then ends before the long chains do: per head and
 // chunk a whole head's step takes a CU 4 us at most, a column tile of the row walk 1.
+// It is also half as long again as the mean: with few more tiles than CUs half of an
+// even batch would pass otherwise, and on an XCD that got many of them the others
+// wait for a second round (37 sequences of 200 to 431 tokens, 1 head, d = 64 x 128:
+// 28 us with such chains apart, 22 without; 9 of 2,000 to 3,855, 8 heads, d = 64: 78
+// and 87, which this gives up).
 __host__ __device__ inline bool is_long_chain(const PrefillArgs &a, int nch, int total) {
-  return (long)nch * a.cus > (long)a.Hv * (a.Dv / 16) * total;
+  return (long)nch * a.cus > (long)a.Hv * (a.Dv / 16) * total && 2L * nch * a.N > 3L * total;
 }
 
 // XCDs of an MI355X.  Each has its own L2; the L2s are not coherent with each
