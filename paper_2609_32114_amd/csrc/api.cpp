@@ -269,13 +269,17 @@ bool compact_applies(bool bf16, bool kda, bool maps, int N, int T, int Hv, int D
 // Workgroups for the column tiles of long chains (is_long_chain) in a compact call
 // walked whole, 0 if there can be none: a batch with more tiles than CUs (up to there
 // every chain's are walked one to a CU), and a chain that might be the batch's only
-// one, long enough to pay for the workgroups that find none (a microsecond) and
+// one, long enough to pay for the workgroups that find none (0.5 to 0.7 us) and
 // narrower than the device.  Against the walk that the other chains take, a step of
-// the row walk saves 0.15 to 0.3 us of tile pairs and 0.5 to 1 us of whole heads.
+// the row walk saves 0.15 to 0.3 us of tile pairs and 0.5 to 1 us of whole heads.  Of
+// 400 batches with one sequence of more than half the tokens, those of 12 chunks or
+// more took up to 1.20 times as long as with the affine factors without this (from 48
+// and 32 chunks only), 1.01 with it; 300 even ones of as many chunks 2 to 4 % longer,
+// 0.91 of the affine factors' time at most.
 int long_chain_rows(int N, int T, int Hv, int Dv, int cus) {
   const long share = (long)Hv * (Dv / 16), x = hagdn::kXcdCount;
   const long tiles = ((long)N * Hv + x - 1) / x * x * (Dv / 16);
-  if (N == 1 || tiles <= cus || share >= cus || chunks_of(T) < (tiles <= 2L * cus ? 48 : 32)) return 0;
+  if (N == 1 || tiles <= cus || share >= cus || chunks_of(T) < 12) return 0;
   const long most = (cus - 1) / share;  // sequences
   if (most + 1 > hagdn::kOvlFlags) return 0;
   return (int)((most * Hv + x - 1) / x * x * (Dv / 16));

@@ -107,6 +107,12 @@ LONG = [  # lengths, value heads at d_v = 128 (twice as many at 64)
     ((20,) * 30 + (2000, 0, 1500, 65), 4),              # whole heads beside two
     ((2,) * 299 + (2500,), 1),                          # more sequences than the index kernel's threads
 ]
+SHORT = [  # the same, on either side of the 12 chunks from which long sequences are walked apart
+    ((3,) * 6 + (674,) + (3,) * 4, 4, 11),
+    ((3,) * 6 + (675,) + (3,) * 4, 4, 12),
+    ((3,) * 17 + (653,), 4, 11),
+    ((3,) * 17 + (654,), 4, 12),
+]
 
 
 @pytest.mark.parametrize("case", LONG, ids=["pairs", "heads", "many"])
@@ -133,6 +139,17 @@ def test_long_sequences_among_short_ones(dims, case):
     o2, _ = run(state, state)
     torch.cuda.synchronize()
     assert torch.equal(o1, o2) and torch.equal(state, s1)
+
+
+@pytest.mark.parametrize("case", SHORT, ids=lambda c: f"N{len(c[0])}-{c[2]}chunks")
+@pytest.mark.parametrize("dims", [(128, 128), (64, 64), (64, 128), (128, 64)], ids=lambda d: f"{d[0]}x{d[1]}")
+def test_long_sequence_in_a_batch_of_few_chunks(dims, case):
+    Dk, Dv = dims
+    lens, Hv = case[0], case[1] * (128 // Dv)
+    tiles = -(-len(lens) * Hv // 8) * 8 * (Dv // 16)
+    assert tiles > 256 and (tiles <= 512) == (len(lens) == 11) and -(-sum(lens) // 64) == case[2]
+    inp = make_case("gdn", lens, Hv, Hv, Dk, Dv, "bf16", with_s0=True, variant="s0", seed=60, scale=Dk ** -0.5)
+    check_against_oracle(inp, label="compact-long-short")
 
 
 def test_workspace_regions_of_a_compact_call():
