@@ -23,6 +23,8 @@ CASES = [
     ("gdn", (1000,), 4, 16, 128, "bf16", 0, False),            # chunk-local kernel, then the walk
     ("gdn", (700, 0, 1, 299), 2, 6, 128, "bf16", 3, False),    # chunk index, segment maps and walks
     ("kda", (900,), 2, 8, 128, "bf16", 3, False),
+    ("gdn", (300, 0, 1, 777, 65), 4, 16, 128, "bf16", 0, False),  # compact head walk
+    ("gdn", (20,) * 7 + (3000,) + (20,) * 8, 4, 4, 128, "bf16", 0, False),  # a long sequence walked apart
     ("gdn", (300, 500), 2, 4, 64, "f32", 0, False),
 ]
 
